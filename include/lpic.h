@@ -134,8 +134,10 @@ typedef struct {
  * are loaded does.  LPIC_FIELD_SEPARATE (lpic_step in 2D): run the three field updates
  * between two particle pushes of consecutive steps (B by dt/2, E by dt, B by dt/2; Sec. 3.3,
  * Algorithm 1) as three grid-wide kernels; without it they run as one kernel over field
- * tiles of up to 64 x 16 cells whenever every box's nx and ny are multiples of a tile edge
- * (>= 8 and >= 4), which computes the same values with one pass over the arrays.
+ * tiles of up to 64 x 16 cells, which computes the same values with one pass over the
+ * arrays, between the caller's E, B and J and a second set of the library's own (9 arrays
+ * per box; where the device has no room for it the three kernels run).  A call of lpic_step
+ * starts and ends on the caller's arrays.
  * LPIC_ESCAPE_REBIN (lpic_step): when a step finds many particles (at least 4096) whose
  * gather stencil or deposit window leaves the staged region of the tile they were sorted
  * into, group them by the tile they are in now (a count, a scan and a scatter of their
@@ -334,7 +336,8 @@ typedef struct {
                                 through global memory (cumulative) */
   int32_t field_tile[2];     /* tile (x, y) of the fused field update between steps; 0 0 when
                                 those updates run as separate kernels (3D, LPIC_FIELD_SEPARATE,
-                                or no tile edge divides every box) */
+                                no room for the second field set) or a window has moved (the
+                                tiles then follow the window) */
 } lpic_stats;
 
 /* Create a simulation over nruns independent boxes.  species[s] belongs to box
@@ -434,8 +437,7 @@ typedef struct {
  * arrays are dropped and counted).  The next step re-sorts.  Field arrays and particle
  * arrays are then in the array frame: box column c is array column (c + x0) mod nx with
  * x0 = (total shift) mod nx (lpic_window_info), so lpic_store_positions returns array-frame
- * x, and box x = array x - x0 dx (mod nx dx).  A simulation that has moved a window runs the
- * field updates between steps as separate kernels.  1 <= m <= nx - 2*3 - 1; at least one
+ * x, and box x = array x - x0 dx (mod nx dx).  1 <= m <= nx - 2*3 - 1; at least one
  * step must have been taken (the alive/dead split of the last sort is used). */
 lpic_status lpic_window_shift(lpic_sim *sim, int32_t r, int32_t m, const lpic_plasma *plasma);
 /* Total cells box r has moved, and fresh particles that found no free slot. */

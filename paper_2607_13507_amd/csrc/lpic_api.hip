@@ -1,5 +1,6 @@
 // C ABI of the PIC hot path: argument validation, descriptor set-up, launch sequencing,
 // the Algorithm 1 step loop with named-stage hooks, HIP graph capture and the autotuner.
+#include <limits.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -808,6 +809,7 @@ struct lpic_sim {
   lpic_options opt{};
   // device tables and scratch
   RunDesc* runs_d = nullptr;
+  RunDesc* runs2_d = nullptr;                // the same runs with the second field set
   SegDesc* segs_d = nullptr;
   int32_t* run_blk_d = nullptr;
   int32_t* seg_blk256_d = nullptr;
@@ -853,7 +855,8 @@ struct lpic_sim {
   bool windows = false;
   bool offsets_valid = false;                // bin offsets of the current particle layout
   int laser_bpr = 0;                         // antenna kernel blocks per run (0: no laser)
-  int64_t* step_dev = nullptr;               // steps taken, on the device (antenna time)
+  int64_t* step_dev = nullptr;               // steps taken, on the device (antenna time): a
+                                             // word per field set
   unsigned int* laser_done = nullptr;        // workgroup counter of the antenna kernel
   int32_t* jshift = nullptr;                 // per run: fixed-point shift of FP32 currents
   int64_t esc_capacity = 0;
@@ -870,9 +873,10 @@ struct lpic_sim {
   int blocks_per_cu_rho = 1;
   // fused 2D field update between steps (launch_yee_mid); mid_tx == 0: not in use
   int mid_tx = 0, mid_ty = 0, mid_ntiles = 0;
+  bool mid_divides = false;                  // the tile divides every box
   int32_t* mid_pfx_d = nullptr;              // nruns + 1 prefix of field tiles
-  void* bands = nullptr;                     // two edge snapshots
-  int64_t band_half = 0;                     // values per snapshot
+  void* set2 = nullptr;                      // E, B and J of the second field set
+  size_t set2_bytes = 0;
   void* old_state = nullptr;
   std::vector<size_t> old_off;
   std::vector<HookEntry> hooks[LPIC_NUM_STAGES];
@@ -881,8 +885,9 @@ struct lpic_sim {
   bool need_sort = true;
   bool need_spread = true;   // the first sort after particles are loaded spreads tiles
   // captured steps keyed by (charge mode, sort, diagnostics, first field updates already
-  // done by the previous step, last field updates merged into the next step's)
-  static constexpr int NGRAPHS = 64;
+  // done by the previous step, last field updates merged into the next step's, field set at
+  // the start, move to the other set)
+  static constexpr int NGRAPHS = 256;
   hipGraphExec_t gexec[NGRAPHS] = {};
   // timing
   bool timing = false;
@@ -923,10 +928,10 @@ bool inner_hooks(const lpic_sim* s) {
   return false;
 }
 
-Tables sim_tables(const lpic_sim* s, const int32_t* seg_blk) {
+Tables sim_tables(const lpic_sim* s, const int32_t* seg_blk, int set = 0) {
   Tables T;
   memset(&T, 0, sizeof(T));
-  T.runs = s->runs_d;
+  T.runs = set ? s->runs2_d : s->runs_d;
   T.segs = s->segs_d;
   T.run_blk = s->run_blk_d;
   T.seg_blk = seg_blk;
@@ -991,7 +996,6 @@ lpic_status configure(lpic_sim* s) {
       d.pml_cells = pm.cells;
       d.psi = s->psi[r];
       d.pml_tab = (const char*)s->psi[r] + pml_psi_bytes(&s->grids[r], pm.cells, s->prec);
-      d.psi_parity = (const int32_t*)((char*)s->step_dev + 128);
     }
     if (d.has_laser) s->laser_bpr = std::max(s->laser_bpr, columns_bpr(&s->grids[r]));
     s->runs_h.push_back(d);
@@ -1034,7 +1038,7 @@ lpic_status configure(lpic_sim* s) {
   s->nbins = bin;
   s->max_chunks = maxch;
   // device tables
-  free_dev(s->runs_d); free_dev(s->segs_d); free_dev(s->run_blk_d);
+  free_dev(s->runs_d); free_dev(s->runs2_d); free_dev(s->segs_d); free_dev(s->run_blk_d);
   free_dev(s->seg_blk256_d); free_dev(s->seg_blk_sort_d);
   free_dev(s->counts); free_dev(s->offsets); free_dev(s->cursor); free_dev(s->mult);
   free_dev(s->chunks); free_dev(s->scan_part);
@@ -1043,7 +1047,7 @@ lpic_status configure(lpic_sim* s) {
   s->rb = Rebin{};
   s->rebin = false;
   s->mult = nullptr;
-  s->runs_d = nullptr; s->segs_d = nullptr; s->run_blk_d = nullptr;
+  s->runs_d = nullptr; s->runs2_d = nullptr; s->segs_d = nullptr; s->run_blk_d = nullptr;
   s->seg_blk256_d = s->seg_blk_sort_d = nullptr;
   s->counts = s->offsets = s->cursor = nullptr;
   s->chunks = nullptr;
@@ -1097,28 +1101,71 @@ lpic_status configure(lpic_sim* s) {
     HIPCHK(prepare_fused(s->prec, s->ndim, s->geo_chain, lds_of_geometry(s, s->geo_chain),
                          s->smem_chain, &s->blocks_per_cu_chain));
   HIPCHK(hipMemcpy(s->step_dev, &s->step, sizeof(int64_t), hipMemcpyHostToDevice));
-  // fused 2D field update between steps: the largest field tile dividing every box
+  // fused 2D field update between steps: the largest field tile that divides every box, or,
+  // where none does, the largest that no box is narrower than by more than half
   free_dev(s->mid_pfx_d);
-  free_dev(s->bands);
   s->mid_pfx_d = nullptr;
-  s->bands = nullptr;
   s->mid_tx = s->mid_ty = s->mid_ntiles = 0;
-  s->band_half = 0;
-  if (s->ndim == 2 && !(t.flags & LPIC_FIELD_SEPARATE) && !s->windows) {
+  s->mid_divides = false;
+  if (s->ndim == 2 && !(t.flags & LPIC_FIELD_SEPARATE)) {
     int tx = MID_MAX_TX, ty = MID_MAX_TY;
     for (int r = 0; r < s->nruns; ++r) {
       while (tx >= 8 && s->grids[r].nx % tx) tx >>= 1;
       while (ty >= 4 && s->grids[r].ny % ty) ty >>= 1;
     }
-    if (tx >= 8 && ty >= 4) {
-      std::vector<int32_t> pfx(1, 0);
-      for (int r = 0; r < s->nruns; ++r)
-        pfx.push_back(pfx.back() + (s->grids[r].nx / tx) * (s->grids[r].ny / ty));
-      s->band_half = (int64_t)pfx.back() * band_values_per_tile(tx, ty);
+    s->mid_divides = tx >= 8 && ty >= 4;
+    if (!s->mid_divides || s->windows || tx * ty < 256) {
+      // (a tile below 256 cells leaves threads idle and reads half its cells again as halo;
+      // 1000 x 600 cells in FP64: 42 us with 8 x 8 tiles that divide it, 26 with 64 x 16)
+      int nxm = INT_MAX, nym = INT_MAX;
+      for (int r = 0; r < s->nruns; ++r) {
+        nxm = std::min(nxm, (int)s->grids[r].nx);
+        nym = std::min(nym, (int)s->grids[r].ny);
+      }
+      if (!s->mid_divides || (nxm >= 64 && nym >= 16)) {
+        tx = MID_MAX_TX;
+        ty = MID_MAX_TY;
+        while (tx > 8 && 2 * nxm <= tx) tx >>= 1;
+        while (ty > 4 && 2 * nym <= ty) ty >>= 1;
+      }
+    }
+    std::vector<int32_t> pfx(1, 0);
+    size_t bytes = 0;
+    const size_t size = s->prec == LPIC_F32_CELLOFS ? 4 : 8;
+    for (int r = 0; r < s->nruns; ++r) {
+      const lpic_grid& g = s->grids[r];
+      const bool mur = g.open_x && s->pmls[r].cells == 0;
+      pfx.push_back(pfx.back() + ((g.nx + mid_shift(mur, g.nx, tx) + tx - 1) / tx) *
+                                     ((g.ny + ty - 1) / ty));
+      bytes += 9 * align256(ncells(&g) * size);
+    }
+    if (!s->set2 || s->set2_bytes != bytes) {
+      free_dev(s->set2);
+      s->set2 = nullptr;
+      // (a box that leaves no room for a second set keeps the separate kernels)
+      if (hipMalloc(&s->set2, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        s->set2 = nullptr;
+      }
+      s->set2_bytes = bytes;
+    }
+    if (s->set2) {
       ALLOC(s->mid_pfx_d, sizeof(int32_t) * pfx.size());
-      ALLOC(s->bands, 2 * (size_t)s->band_half * (s->prec == LPIC_F32_CELLOFS ? 4 : 8));
+      ALLOC(s->runs2_d, sizeof(RunDesc) * s->nruns);
       HIPCHK(hipMemcpy(s->mid_pfx_d, pfx.data(), sizeof(int32_t) * pfx.size(),
                        hipMemcpyHostToDevice));
+      std::vector<RunDesc> runs2(s->runs_h);
+      char* at = (char*)s->set2;
+      for (int r = 0; r < s->nruns; ++r) {
+        runs2[r].psi_half = 1;
+        for (int k = 0; k < 9; ++k) {
+          runs2[r].f[k] = at;
+          at += align256(ncells(&s->grids[r]) * size);
+        }
+      }
+      HIPCHK(hipMemcpy(s->runs2_d, runs2.data(), sizeof(RunDesc) * s->nruns, hipMemcpyHostToDevice));
+      // without species nothing clears the second set's J: it starts and stays zero
+      HIPCHK(hipMemset(s->set2, 0, bytes));
       s->mid_tx = tx;
       s->mid_ty = ty;
       s->mid_ntiles = pfx.back();
@@ -1212,45 +1259,28 @@ lpic_status enqueue_fixed_shift(lpic_sim* s, hipStream_t st) {
   return last_launch("fixed-point shift");
 }
 
-int log2i(int v) {
-  int l = 0;
-  while ((1 << l) < v) ++l;
-  return l;
-}
-
-// The edge snapshots of the fused 2D field update; the parity word sits in the device step
-// block.
-FieldBands sim_bands(const lpic_sim* s) {
-  FieldBands b;
-  memset(&b, 0, sizeof(b));
-  b.base = s->bands;
-  b.half = s->band_half;
-  b.tile_pfx = s->mid_pfx_d;
-  b.parity = (int32_t*)((char*)s->step_dev + 128);
-  b.step = s->laser_bpr > 0 ? s->step_dev : nullptr;
-  b.tx = s->mid_tx;
-  b.ty = s->mid_ty;
-  b.lx = log2i(s->mid_tx);
-  b.ly = log2i(s->mid_ty);
-  return b;
-}
-
 // The device work of one step between the LOOP_START and LOOP_END hooks.  With hooks at the
 // inner stages the host runs them in between (eager mode only).
 // first_full: the previous step deferred its last E half (skip_last), so this step's first
 // E update covers both halves at once: between them B does not change and J is the same
 // array, so E + (dt/2)(curl B - J) twice is E + dt (curl B - J).  With the fused 2D field
 // update the previous step already did all of it (its B half, this full E update and this
-// step's first B half), and this step only clears the sources.
+// step's first B half) and cleared J, and this step only clears the charge it accumulates.
+// set: the field set (FieldSets) that holds the fields at the start; the fused update of a
+// step that defers its last E half moves them to the other one.  move: the step's first
+// updates move them too (one call starts and ends on the caller's set, so a call with an odd
+// number of fused updates moves once more).
 // rho: the charge this step accumulates (deposit's with_rho): 1 on a diagnostic step, or
 // with chained charge 2 on the step before one and 3 on the diagnostic step; 0 otherwise.
 lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread, bool diag,
                          bool eager_hooks, bool capturing, bool first_full, bool skip_last,
-                         int rho) {
-  const Tables Tc = sim_tables(s, nullptr);
-  const Tables Ts = sim_tables(s, s->seg_blk_sort_d);
+                         int rho, int set, bool move) {
+  const Tables T0 = sim_tables(s, nullptr, set);
+  if (move) set ^= 1;
+  const Tables Tc = sim_tables(s, nullptr, set);
+  const Tables Ts = sim_tables(s, s->seg_blk_sort_d, set);
   const bool mid = s->mid_tx > 0;
-  const FieldBands bands = mid ? sim_bands(s) : FieldBands{};
+  int64_t* clock = s->laser_bpr > 0 ? s->step_dev : nullptr;
   if (diag) {
     launch_diag_clear(Tc, s->nruns, st);
     CHK(last_launch("diag clear"));
@@ -1258,19 +1288,19 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
   // (the charge arrays are only written, and so only cleared, by the steps that accumulate
   // charge: both on a diagnostic step, rho0 before it and rho1 on it with chained charge)
   if (first_full && mid) {
-    const int zero = rho == 1 ? 1 : (rho == 2 ? 3 : (rho == 3 ? 4 : 0));
-    launch_clear_sources(Tc, s->prec, s->ndim, s->nblk_cells, zero, bands.parity,
-                         s->laser_bpr > 0 ? s->step_dev : nullptr, st);
-    CHK(last_launch("clear sources"));
+    if (rho) {
+      launch_clear_charge(Tc, s->prec, s->ndim, s->nblk_cells, rho == 1 ? 1 : (rho == 2 ? 3 : 4),
+                          st);
+      CHK(last_launch("clear charge"));
+    }
   } else {
     // field half update t -> t + dt/2 (E first), clearing J for the deposit
     const int zero = rho == 1 ? 1 : (rho == 2 ? 3 : (rho == 3 ? 4 : 2));
-    launch_yee(Tc, s->prec, s->ndim, s->nblk_cells, 0, first_full ? 1.0 : 0.5, zero,
-               first_full ? 2 : 1, st);
+    const RunDesc* out = move ? Tc.runs : nullptr;
+    launch_yee(T0, s->prec, s->ndim, s->nblk_cells, 0, first_full ? 1.0 : 0.5, zero,
+               first_full ? 2 : 1, st, out, clock);
     CHK(last_launch("yee E"));
-    // a step whose last field updates go to the fused update publishes the tile edges
-    launch_yee(Tc, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st,
-               (mid && skip_last) ? &bands : nullptr);
+    launch_yee(T0, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st, out);
     CHK(last_launch("yee B"));
   }
   if (eager_hooks) CHK(run_hooks(s, LPIC_STAGE_MAXWELL_1));
@@ -1356,8 +1386,8 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
   }
   if (s->laser_bpr > 0 && !(skip_last && mid)) {   // antenna current at t = (step + 1) dt
     // (a fused field update adds it itself)
-    launch_laser(Tc, s->prec, s->ndim, s->nruns, s->laser_bpr, 0.0, s->step_dev, s->laser_done,
-                 st);
+    launch_laser(Tc, s->prec, s->ndim, s->nruns, s->laser_bpr, 0.0, s->step_dev + set,
+                 s->laser_done, st);
     CHK(last_launch("laser"));
   }
   if (eager_hooks) {
@@ -1371,7 +1401,14 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
     Tm.run_blk = s->mid_pfx_d;
     bool pml = false;
     for (const lpic_pml& p : s->pmls) pml = pml || p.cells > 0;
-    launch_yee_mid(Tm, s->prec, s->mid_ntiles, bands, pml, st);
+    FieldSets sets;
+    sets.out = set ? s->runs_d : s->runs2_d;
+    sets.clock_in = clock ? clock + set : nullptr;
+    sets.clock_out = clock ? clock + (set ^ 1) : nullptr;
+    sets.tx = s->mid_tx;
+    sets.ty = s->mid_ty;
+    sets.species = s->nsegs > 0;
+    launch_yee_mid(Tm, s->prec, s->mid_ntiles, sets, pml, st);
     CHK(last_launch("yee fused"));
   } else {
     // field half update t + dt/2 -> t + dt (B first)
@@ -1488,6 +1525,7 @@ void lpic_sim_destroy(lpic_sim* s) {
   if (!s) return;
   if (s->stream) (void)hipStreamSynchronize(s->stream);
   drop_graphs(s);
+  free_dev(s->runs2_d);
   for (auto& e : s->ev_pending) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
   for (auto& e : s->ev_free) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
   free_dev(s->runs_d); free_dev(s->segs_d); free_dev(s->run_blk_d);
@@ -1501,7 +1539,7 @@ void lpic_sim_destroy(lpic_sim* s) {
   free_dev(s->rb_items); free_dev(s->esc2_items); free_dev(s->esc2_count);
   free_dev(s->esc_rec); free_dev(s->rb_rec); free_dev(s->esc_keys);
   free_dev(s->wmax); free_dev(s->jshift); free_dev(s->step_dev);
-  free_dev(s->mid_pfx_d); free_dev(s->bands);
+  free_dev(s->mid_pfx_d); free_dev(s->set2);
   free_dev(s->old_state);
   for (void* p : s->psi) free_dev(p);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
@@ -1538,6 +1576,12 @@ lpic_status lpic_step(lpic_sim* s, int32_t nsteps) {
   const bool chain = s->chain && !hooks && !split && s->opt.diag_interval >= 2;
   int prev_rho = 0;
   bool e_half_pending = false;
+  // the field set in use, and whether the first step's updates move to the other one
+  int set = 0;
+  bool move = false;
+  if (s->mid_tx > 0 && !hooks)
+    for (int n = 0; n + 1 < nsteps; ++n)
+      if (s->opt.diag_interval == 0 || ((s->step + n + 1) % s->opt.diag_interval) != 0) move = !move;
   for (int n = 0; n < nsteps; ++n) {
     CHK(run_hooks(s, LPIC_STAGE_LOOP_START));
     const bool do_sort = s->need_sort || (s->step % s->opt.sort_interval) == 0;
@@ -1559,13 +1603,13 @@ lpic_status lpic_step(lpic_sim* s, int32_t nsteps) {
     // the one-off spreading sort runs eagerly; captured sort steps use the plain sort unless
     // every sort spreads
     if (use_graph && (!spread || always_spread)) {
-      const int gi = rho * 16 + (do_sort ? 8 : 0) + (diag ? 4 : 0) + (first_full ? 2 : 0) +
-                     (skip_last ? 1 : 0);
+      const int gi = (move ? 128 : 0) + set * 64 + rho * 16 + (do_sort ? 8 : 0) + (diag ? 4 : 0) +
+                     (first_full ? 2 : 0) + (skip_last ? 1 : 0);
       if (!s->gexec[gi]) {
         hipGraph_t g = nullptr;
         HIPCHK(hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
         lpic_status st = enqueue_step(s, s->cap_stream, do_sort, spread, diag, false, true,
-                                      first_full, skip_last, rho);
+                                      first_full, skip_last, rho, set, move);
         hipError_t ee = hipStreamEndCapture(s->cap_stream, &g);
         if (st != LPIC_OK) { if (g) (void)hipGraphDestroy(g); return st; }
         if (ee != hipSuccess) return fail(LPIC_EHIP, "graph capture: %s", hipGetErrorString(ee));
@@ -1577,8 +1621,11 @@ lpic_status lpic_step(lpic_sim* s, int32_t nsteps) {
       if (do_sort && s->nsegs > 0) swap_host_buffers(s);
     } else {
       CHK(enqueue_step(s, s->stream, do_sort, spread, diag, true, false, first_full, skip_last,
-                       rho));
+                       rho, set, move));
     }
+    if (move) set ^= 1;
+    if (skip_last && s->mid_tx > 0) set ^= 1;
+    move = false;
     if (do_sort && s->nsegs > 0) {
       ++s->sorts;
       s->need_sort = false;
@@ -1622,8 +1669,8 @@ lpic_status lpic_get_stats(lpic_sim* s, lpic_stats* out) {
   HIPCHK(hipStreamSynchronize(s->stream));
   HIPCHK(hipMemcpy(&esc, s->escapes, sizeof(esc), hipMemcpyDeviceToHost));
   out->halo_escapes = (int64_t)esc;
-  out->field_tile[0] = s->mid_tx;
-  out->field_tile[1] = s->mid_ty;
+  out->field_tile[0] = s->windows ? 0 : s->mid_tx;
+  out->field_tile[1] = s->windows ? 0 : s->mid_ty;
   return LPIC_OK;
 }
 
@@ -1766,13 +1813,9 @@ lpic_status lpic_window_shift(lpic_sim* s, int32_t r, int32_t m, const lpic_plas
         !std::isfinite(plasma->uz))
       return fail(LPIC_EINVAL, "bad plasma density or momentum");
   }
-  if (!s->windows) {   // the fused field update assumes the origin at column 0
-    s->windows = true;
-    s->mid_tx = s->mid_ty = s->mid_ntiles = 0;
-    drop_graphs(s);
-  }
+  s->windows = true;
   Tables T = sim_tables(s, s->seg_blk256_d);
-  launch_window_shift(T, s->prec, s->ndim, r, m, (int64_t)g.ny, s->nblk_p256, s->stream);
+  launch_window_shift(T, s->runs2_d, s->prec, s->ndim, r, m, (int64_t)g.ny, s->nblk_p256, s->stream);
   CHK(last_launch("window shift"));
   s->x0[r] = (s->x0[r] + m) % g.nx;
   s->runs_h[r].x0 = s->x0[r];

@@ -48,11 +48,10 @@ struct RunDesc {
   double* diag;                    // DIAG_NUM device accumulators
   LaserDesc laser;
   // convolutional PML at the open x ends (pml_cells = 0: Mur condition instead)
-  int32_t pml_cells, pad1;
+  int32_t pml_cells, psi_half;     // psi_half: the half of psi that goes with these fields
   void* psi;                       // 2 halves x 4 components x rows x 2 pml_cells values
   const void* pml_tab;             // b, c, 1/kappa per slot for a half step dt/2: E side
                                    // (2 pml_cells slots), then B side
-  const int32_t* psi_parity;       // which half is current (the fused field update's parity)
 };
 
 // Box column of array column i, and back (x0: the moving window's origin).

@@ -42,49 +42,46 @@ struct OldState {
 
 constexpr int SORT_BLOCK = 2048;   // particles per workgroup of the sort kernels
 
-// Snapshot of the tile edges for the fused 2D field update (launch_yee_mid): the domain is
-// cut into field tiles of tx x ty cells, and every tile publishes, per field component
-// (Ex Ey Ez Bx By Bz), the values of its first two and its last column (3 ty values) and
-// of its first two and its last row (3 tx values).  Two buffers of `half` values: the
-// word *parity names the one holding the present fields.
-struct FieldBands {
-  void* base;
-  int64_t half;
-  const int32_t* tile_pfx;     // nruns + 1 prefix of field tiles (one workgroup per tile)
-  int32_t* parity;
-  const int64_t* step;         // antenna clock (steps taken); NULL: no run has an antenna
-  int32_t tx, ty;              // powers of two, tx <= MID_MAX_TX, ty <= MID_MAX_TY
-  int32_t lx, ly;              // their log2
+// The two field sets of a 2D simulation: the caller's E, B and J (with the first half of
+// each run's psi and the first clock word) and a second set of the library's own.  The fused
+// field update reads one and writes the other, so no tile reads a cell that another one
+// writes; a call of lpic_step starts and ends on the caller's set.
+struct FieldSets {
+  const RunDesc* out;          // the runs with the arrays of the set that is written
+  int64_t* clock_in;           // antenna clock (steps taken) of the set that is read, NULL: no
+  int64_t* clock_out;          // run has an antenna; and of the other one
+  int32_t tx, ty;              // field tile: powers of two, tx <= MID_MAX_TX, ty <= MID_MAX_TY
+  bool species;                // some run has species (else J is zero)
 };
 constexpr int MID_MAX_TX = 64, MID_MAX_TY = 16;
-inline int64_t band_values_per_tile(int tx, int ty) { return 6 * 3 * (int64_t)(tx + ty); }
+// Columns by which the tiles of an open box with the Mur condition start before the box:
+// its last column must not be the first of a tile (see k_yee_mid).
+__host__ __device__ inline int mid_shift(bool mur, int nx, int tx) {
+  return mur && nx % tx == 1 ? 1 : 0;
+}
 
 // which = 0: E update (zero_j = 1 also clears J and rho, 2 J only, 3 J and rho0, 4 J and
 // rho1), 1: B update.  halves = 2: the E
 // update stands for two equal half updates (open x ends apply their condition twice).
-// bands (B update in 2D only, may be NULL): also publish E and the new B of the tile edges
-// into the snapshot buffer named by *parity, for a fused update that follows.
+// out != NULL: the runs of the other field set, which the update writes (an E update, then a
+// B update, move a simulation there; clock: its two antenna clock words or NULL).
 void launch_yee(const Tables& T, int prec, int dim, int nblocks, int which, double frac,
-                int zero_j, int halves, hipStream_t st, const FieldBands* bands = nullptr);
+                int zero_j, int halves, hipStream_t st, const RunDesc* out = nullptr,
+                int64_t* clock = nullptr);
 // The three field updates between two particle pushes of 2D steps, fused: B by dt/2, E by
 // dt (two merged halves, with the J in place), B by dt/2 -- the last half update of one
-// step and the first two of the next.  T.run_blk must be the tile prefix (one workgroup
-// per field tile).  Reads the snapshot named by *parity and writes the other one; J is
-// only read.  Runs with an antenna get its current of this step (t = (*step + 1) dt) added
-// in the E update instead of through the array, so the antenna kernel is not launched for
-// the step.  The next launch on the stream must be launch_clear_sources with
-// flip = bands.parity and clock = bands.step: it clears J for the next deposit, names the
-// new snapshot and advances the antenna clock.  pml: some run has PML layers (their psi
-// follow the same two-half scheme, with the same parity word); false selects kernels
-// without that code.
-void launch_yee_mid(const Tables& T, int prec, int ntiles, const FieldBands& bands, bool pml,
+// step and the first two of the next, from the set of T into the other one, whose J is
+// cleared for the next deposit.  T.run_blk must be the tile prefix (one workgroup
+// per field tile).  Runs with an antenna get its current of this step (t = (*clock_in + 1)
+// dt) added in the E update instead of through the array, so the antenna kernel is not
+// launched for the step.  pml: some run has PML layers (their psi move between their two
+// halves with the fields); false selects kernels without that code.
+void launch_yee_mid(const Tables& T, int prec, int ntiles, const FieldSets& sets, bool pml,
                     hipStream_t st);
-// J := 0 (and the charge arrays when with_rho) over every cell of every run (nblocks: the
-// 256-cell blocks of T.run_blk).  flip != NULL: also *flip ^= 1 and, clock != NULL,
-// *clock += 1 (one thread).
-// with_rho: 1 also clears both charge arrays, 3 rho0 only, 4 rho1 only.
-void launch_clear_sources(const Tables& T, int prec, int dim, int nblocks, int with_rho,
-                          int32_t* flip, int64_t* clock, hipStream_t st);
+// The charge arrays := 0 over every cell of every run (nblocks: the 256-cell blocks of
+// T.run_blk).  with_rho: 1 both, 3 rho0 only, 4 rho1 only.
+void launch_clear_charge(const Tables& T, int prec, int dim, int nblocks, int with_rho,
+                         hipStream_t st);
 // Laser antennas of the runs that have one (bpr workgroups of 256 (j, k) cells per run).
 // step != NULL: t = (*step + 1) dt, and the launch advances *step (done: a zeroed counter).
 void launch_laser(const Tables& T, int prec, int dim, int nruns, int bpr, double t,
@@ -179,9 +176,10 @@ void launch_zero_doubles(double* p, int n, hipStream_t st);
 void launch_diag_clear(const Tables& T, int nruns, hipStream_t st);
 // Moving window of run `run` (open x ends): clear the fields of its first m box columns,
 // remove the particles there (nblk_part: 256-particle blocks of all segments, T.seg_blk the
-// matching prefix), then advance the run's origin x0 by m on the device.
-void launch_window_shift(const Tables& T, int prec, int dim, int run, int m, int64_t rows,
-                         int nblk_part, hipStream_t st);
+// matching prefix), then advance the run's origin x0 by m on the device (other: the run
+// table of the second field set, or NULL).
+void launch_window_shift(const Tables& T, RunDesc* other, int prec, int dim, int run, int m,
+                         int64_t rows, int nblk_part, hipStream_t st);
 // Fresh plasma for the m box columns inside the right-hand margin of segment seg's run (after
 // launch_window_shift): count = m * ny * px * py particles on a px x py lattice per cell,
 // written after the segment's alive particles of the last sort (offsets) plus `used`.

@@ -137,21 +137,17 @@ __device__ __forceinline__ int64_t pml_index(const RunDesc& r, int half, int com
   return ((int64_t)(half * 4 + comp) * rows + row) * (2 * r.pml_cells) + slot;
 }
 
-__device__ __forceinline__ int pml_half(const RunDesc& r) {
-  return r.psi_parity ? (*r.psi_parity & 1) : 0;
-}
-
-// One stretched x difference of component comp at (row, slot), in place in the current
-// half: advances psi over `steps` half-step updates with the same plain difference D (an E
-// update of a whole dt made of two merged halves takes steps = 2 and returns the mean of
-// the two stretched differences) and returns the stretched difference.
+// One stretched x difference of component comp at (row, slot): advances psi from half `from`
+// to half `to` (the same one in place) over `steps` half-step updates with the same plain
+// difference D (an E update of a whole dt made of two merged halves takes steps = 2 and
+// returns the mean of the two stretched differences) and returns the stretched difference.
 template <typename R>
-__device__ __forceinline__ R pml_stretch(const RunDesc& r, int comp, int64_t row, int slot,
-                                         int steps, R D) {
+__device__ __forceinline__ R pml_stretch(const RunDesc& r, int from, int to, int comp,
+                                         int64_t row, int slot, int steps, R D) {
   R b, c, ik;
   pml_coef<R>(r, comp >= 2, slot, b, c, ik);
-  R* psi = (R*)r.psi + pml_index(r, pml_half(r), comp, row, slot);
-  const R p1 = b * *psi + c * D;
+  R* psi = (R*)r.psi + pml_index(r, to, comp, row, slot);
+  const R p1 = b * ((const R*)r.psi)[pml_index(r, from, comp, row, slot)] + c * D;
   if (steps == 1) {
     *psi = p1;
     return D * ik + p1;
@@ -161,15 +157,24 @@ __device__ __forceinline__ R pml_stretch(const RunDesc& r, int comp, int64_t row
   return D * ik + R(0.5) * (p1 + p2);
 }
 
-template <typename R, int DIM>
-__global__ __launch_bounds__(256) void k_yee_e(Tables T, double frac, int zero_j, int halves) {
+// MOVE (out: the runs of a simulation's other field set, FieldSets): E is written there
+// instead of in place, with J cleared in both sets and the antenna clock carried over.
+template <typename R, int DIM, bool MOVE>
+__global__ __launch_bounds__(256) void k_yee_e(Tables T, double frac, int zero_j, int halves,
+                                               const RunDesc* out, int64_t* clock) {
   int blk;
-  const RunDesc& r = run_of(T, cell_block(T, blk));
+  const int ri = cell_block(T, blk);
+  const RunDesc& r = run_of(T, ri);
+  const RunDesc& ro = MOVE ? out[ri] : r;
+  if (MOVE && clock && blockIdx.x == 0 && threadIdx.x == 0) clock[1] = clock[0];
   CellIdx x;
   if (!cell_index(r, blk, DIM, x)) return;
-  gptr<R> f[F_NUM];
+  gptr<R> f[F_NUM], o[F_NUM];
 #pragma unroll
-  for (int c = 0; c < F_NUM; ++c) f[c] = gp((R*)r.f[c]);
+  for (int c = 0; c < F_NUM; ++c) {
+    f[c] = gp((R*)r.f[c]);
+    o[c] = MOVE ? gp((R*)ro.f[c]) : f[c];
+  }
   const double h = frac * r.dt;
   const R hx = R(h / r.dx), hy = R(h / r.dy), hz = R(DIM == 3 ? h / r.dz : 0.0), hh = R(h);
   R dex, dey, dez;
@@ -178,26 +183,28 @@ __global__ __launch_bounds__(256) void k_yee_e(Tables T, double frac, int zero_j
   if (ps >= 0) {   // in a PML layer: the x differences of Bz and By are stretched
     const R dbz = f[F_BZ][x.c] - f[F_BZ][x.cim], dby = f[F_BY][x.c] - f[F_BY][x.cim];
     const int64_t row = x.row;
-    dey += hx * (dbz - pml_stretch<R>(r, 0, row, ps, halves, dbz));
-    dez -= hx * (dby - pml_stretch<R>(r, 1, row, ps, halves, dby));
+    dey += hx * (dbz - pml_stretch<R>(r, r.psi_half, ro.psi_half, 0, row, ps, halves, dbz));
+    dez -= hx * (dby - pml_stretch<R>(r, r.psi_half, ro.psi_half, 1, row, ps, halves, dby));
   }
-  f[F_EX][x.c] += dex;
+  o[F_EX][x.c] = f[F_EX][x.c] + dex;
   const int bxi = box_x(r, x.i);   // box column (a moving window shifts the arrays' origin)
   const bool mur = r.open_x && r.pml_cells == 0;
   if (mur && bxi == 1) {   // Mur for column 0 (same j, k)
     const R ey1 = f[F_EY][x.c], ez1 = f[F_EZ][x.c];
-    f[F_EY][x.cim] = mur_edge<R>(f[F_EY][x.cim], ey1, dey, h, r.dx, halves);
-    f[F_EZ][x.cim] = mur_edge<R>(f[F_EZ][x.cim], ez1, dez, h, r.dx, halves);
+    o[F_EY][x.cim] = mur_edge<R>(f[F_EY][x.cim], ey1, dey, h, r.dx, halves);
+    o[F_EZ][x.cim] = mur_edge<R>(f[F_EZ][x.cim], ez1, dez, h, r.dx, halves);
   }
   if (!(mur && bxi == 0)) {   // column 0 of an open end: set by the thread of column 1
-    f[F_EY][x.c] += dey;
-    f[F_EZ][x.c] += dez;
+    o[F_EY][x.c] = f[F_EY][x.c] + dey;
+    o[F_EZ][x.c] = f[F_EZ][x.c] + dez;
   }
   if (zero_j) {   // 1: clear J and the charge arrays (when given); 2: J only; 3: J and
                   // rho0; 4: J and rho1
-    f[F_JX][x.c] = R(0);
-    f[F_JY][x.c] = R(0);
-    f[F_JZ][x.c] = R(0);
+#pragma unroll
+    for (int c = F_JX; c <= F_JZ; ++c) {
+      f[c][x.c] = R(0);
+      if (MOVE) o[c][x.c] = R(0);
+    }
     if ((zero_j == 1 || zero_j == 3) && f[F_R0]) f[F_R0][x.c] = R(0);
     if ((zero_j == 1 || zero_j == 4) && f[F_R1]) f[F_R1][x.c] = R(0);
   }
@@ -220,46 +227,22 @@ __device__ __forceinline__ bool antenna_current(const RunDesc& r, double t_abs, 
   return true;
 }
 
-// ---------------------------------------------------------------------------------------
-// Tile-edge snapshot of the fused 2D field update (FieldBands).  Cell (i, j) of a run lies
-// in field tile (i >> lx, j >> ly) at (li, lj); the tile's slice of component k starts at
-// ((tile0 + tile) * 6 + k) * 3 (tx + ty) and holds columns li = 0, 1, tx-1 (ty values
-// each), then rows lj = 0, 1, ty-1 (tx values each).  A corner cell is in both.
-// ---------------------------------------------------------------------------------------
-__device__ __forceinline__ int band_col(int li, int tx) { return li <= 1 ? li : (li == tx - 1 ? 2 : -1); }
-
-// Snapshot index of cell (i, j), component k; the cell must lie on an edge band.
-__device__ __forceinline__ int64_t band_at(const FieldBands& Bd, int ntx, int64_t tile0, int i,
-                                          int j, int k) {
-  const int ti = i >> Bd.lx, tj = j >> Bd.ly;
-  const int li = i - (ti << Bd.lx), lj = j - (tj << Bd.ly);
-  const int64_t base = ((tile0 + (int64_t)tj * ntx + ti) * 6 + k) * (3 * (Bd.tx + Bd.ty));
-  const int cb = band_col(li, Bd.tx);
-  if (cb >= 0) return base + cb * Bd.ty + lj;
-  return base + 3 * Bd.ty + band_col(lj, Bd.ty) * Bd.tx + li;
-}
-
-// Publishes value v of a cell at (li, lj) of a tile whose slice of component 0 starts at
-// `base` (stride 3 (tx + ty) per component).
-template <typename R>
-__device__ __forceinline__ void band_put(R* out, const FieldBands& Bd, int64_t base, int li,
-                                         int lj, int k, R v) {
-  const int64_t b = base + (int64_t)k * (3 * (Bd.tx + Bd.ty));
-  const int cb = band_col(li, Bd.tx), rb = band_col(lj, Bd.ty);
-  if (cb >= 0) out[b + cb * Bd.ty + lj] = v;
-  if (rb >= 0) out[b + 3 * Bd.ty + rb * Bd.tx + li] = v;
-}
-
-template <typename R, int DIM>
-__global__ __launch_bounds__(256) void k_yee_b(Tables T, double frac, FieldBands Bd) {
+// MOVE: the E of the other field set (written by the E update before), the B of this one,
+// the new B to the other one.
+template <typename R, int DIM, bool MOVE>
+__global__ __launch_bounds__(256) void k_yee_b(Tables T, double frac, const RunDesc* out) {
   int blk;
   const int ri = cell_block(T, blk);
   const RunDesc& r = run_of(T, ri);
+  const RunDesc& ro = MOVE ? out[ri] : r;
   CellIdx x;
   if (!cell_index(r, blk, DIM, x)) return;
-  gptr<R> f[F_NUM];
+  gptr<R> f[6], o[6];
 #pragma unroll
-  for (int c = 0; c < F_NUM; ++c) f[c] = gp((R*)r.f[c]);
+  for (int c = 0; c < 6; ++c) {
+    o[c] = gp((R*)ro.f[c]);
+    f[c] = c < F_BX ? o[c] : gp((R*)r.f[c]);
+  }
   const double h = frac * r.dt;
   const R hx = R(h / r.dx), hy = R(h / r.dy), hz = R(DIM == 3 ? h / r.dz : 0.0);
   R dbx, dby, dbz;
@@ -268,69 +251,55 @@ __global__ __launch_bounds__(256) void k_yee_b(Tables T, double frac, FieldBands
   if (ps >= 0) {   // in a PML layer: the x differences of Ez and Ey are stretched
     const R dez = f[F_EZ][x.cip] - f[F_EZ][x.c], dey = f[F_EY][x.cip] - f[F_EY][x.c];
     const int64_t row = x.row;
-    dby -= hx * (dez - pml_stretch<R>(r, 2, row, ps, 1, dez));
-    dbz += hx * (dey - pml_stretch<R>(r, 3, row, ps, 1, dey));
+    dby -= hx * (dez - pml_stretch<R>(r, r.psi_half, ro.psi_half, 2, row, ps, 1, dez));
+    dbz += hx * (dey - pml_stretch<R>(r, r.psi_half, ro.psi_half, 3, row, ps, 1, dey));
   }
-  const R bx = f[F_BX][x.c] + dbx;
-  f[F_BX][x.c] = bx;
+  o[F_BX][x.c] = f[F_BX][x.c] + dbx;
   const int bxi = box_x(r, x.i);   // box column (a moving window shifts the arrays' origin)
   const bool mur = r.open_x && r.pml_cells == 0;
-  const bool edge_in = mur && bxi == r.nx - 2;
   const bool edge = mur && bxi == r.nx - 1;
-  R by_e = R(0), bz_e = R(0);
-  if (edge_in) {   // Mur for column nx-1 (same j, k)
+  if (mur && bxi == r.nx - 2) {   // Mur for column nx-1 (same j, k)
     const R by1 = f[F_BY][x.c], bz1 = f[F_BZ][x.c];
-    by_e = mur_edge<R>(f[F_BY][x.cip], by1, dby, h, r.dx, 1);
-    bz_e = mur_edge<R>(f[F_BZ][x.cip], bz1, dbz, h, r.dx, 1);
-    f[F_BY][x.cip] = by_e;
-    f[F_BZ][x.cip] = bz_e;
+    o[F_BY][x.cip] = mur_edge<R>(f[F_BY][x.cip], by1, dby, h, r.dx, 1);
+    o[F_BZ][x.cip] = mur_edge<R>(f[F_BZ][x.cip], bz1, dbz, h, r.dx, 1);
   }
-  R by = R(0), bz = R(0);
   if (!edge) {   // last column of an open end: set by column nx-2
-    by = f[F_BY][x.c] + dby;
-    bz = f[F_BZ][x.c] + dbz;
-    f[F_BY][x.c] = by;
-    f[F_BZ][x.c] = bz;
-  }
-  if (DIM == 2 && Bd.base) {
-    const int j = (int)(x.c / r.nx);
-    const int ti = x.i >> Bd.lx, tj = j >> Bd.ly;
-    const int li = x.i - (ti << Bd.lx), lj = j - (tj << Bd.ly);
-    const int ntx = r.nx >> Bd.lx;
-    R* out = (R*)Bd.base + (int64_t)(*Bd.parity & 1) * Bd.half;
-    const int64_t base = (Bd.tile_pfx[ri] + (int64_t)tj * ntx + ti) * 6 * (3 * (Bd.tx + Bd.ty));
-    if (band_col(li, Bd.tx) >= 0 || band_col(lj, Bd.ty) >= 0) {
-      band_put(out, Bd, base, li, lj, 0, (R)f[F_EX][x.c]);
-      band_put(out, Bd, base, li, lj, 1, (R)f[F_EY][x.c]);
-      band_put(out, Bd, base, li, lj, 2, (R)f[F_EZ][x.c]);
-      band_put(out, Bd, base, li, lj, 3, bx);
-      if (!edge) {
-        band_put(out, Bd, base, li, lj, 4, by);
-        band_put(out, Bd, base, li, lj, 5, bz);
-      }
-    }
-    if (edge_in) {   // column nx-1: the last column of this thread's tile (tx divides nx)
-      band_put(out, Bd, base, li + 1, lj, 4, by_e);
-      band_put(out, Bd, base, li + 1, lj, 5, bz_e);
-    }
+    o[F_BY][x.c] = f[F_BY][x.c] + dby;
+    o[F_BZ][x.c] = f[F_BZ][x.c] + dbz;
   }
 }
 
 // ---------------------------------------------------------------------------------------
 // The field updates between the particle pushes of two 2D steps in one pass per tile:
 // B += (dt/2) (-curl E), E += dt (curl B - J), B += (dt/2) (-curl E) -- the same arithmetic,
-// cell by cell, as k_yee_b, k_yee_e (two merged halves) and k_yee_b in sequence.  The output
-// tile [a, a+tx) x [c, c+ty) needs E on [a-1, a+tx+2) x [c-1, c+ty+2) and B on
-// [a-1, a+tx+1) x [c-1, c+ty+1); its own cells come from the field arrays, the others from
-// the neighbours' edge snapshot (never from the arrays, which the neighbours overwrite during
-// this launch).  Cells outside the output tile are recomputed redundantly.  With open x
+// cell by cell, as k_yee_b, k_yee_e (two merged halves) and k_yee_b in sequence, from one
+// field set into the other (FieldSets), where it also clears J for the next deposit.  The
+// output tile [a, a+tx) x [c, c+ty) needs E on [a-1, a+tx+2) x [c-1, c+ty+2) and B on
+// [a-1, a+tx+1) x [c-1, c+ty+1); cells outside the output tile are recomputed redundantly.
+// Columns are box columns (array column + origin of a moving window), tiles need not divide
+// the box: cells past its end are images of wrapped ones and are not stored.  With open x
 // ends, values computed for a wrapped image of column 0 or nx-1 only feed components that
-// the open-end condition replaces, so they are left as computed.
+// the open-end condition replaces, so they are left as computed; the condition takes column
+// nx-1 from its neighbour nx-2 in the same tile, so a box of 1 + k tx columns starts its
+// tiles one column before the box (mid_shift).
+// Bound by memory: 60 bytes a cell in FP32 (48 without species: J is zero and not read) and
+// 12 of cleared J.  Reading the neighbours' cells from the arrays of a set that no tile
+// writes replaces a snapshot of every tile's edges (23% more bytes, tiles that divide the
+// boxes) and a clearing kernel per step.  FP32, before and after, clearing included: 2048 x
+// 1024 cells of vacuum 37.8 us a step and 22.6, the same box with 16-cell layers 52.3 and
+// 43.6; 8192 x 512 under a moving window (three separate kernels before) 136 and 71.  Of
+// the 22.6, the tile order by XCD gives 4 (26.7 with tiles dealt to the XCDs in turn: every
+// halo then comes from another L2).
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ int wrap_once(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
-
 template <int N> struct Log2 { static constexpr int v = 1 + Log2<N / 2>::v; };
 template <> struct Log2<1> { static constexpr int v = 0; };
+
+// v modulo n for v in [-n, ..): nearly always within one n.
+__device__ __forceinline__ int wrap_near_box(int v, int n) {
+  if (v < 0) v += n;
+  if (v >= n) v -= n;
+  return v >= n ? v % n : v;
+}
 
 // Cell h of the halo ring of a region (TX + 1 + HI) x (TY + 1 + HI) whose interior TX x TY
 // starts at (1, 1): first the 1 + HI full rows (v = 0, TY + 1, ..), then the 1 + HI columns
@@ -350,121 +319,151 @@ __device__ __forceinline__ void ring_cell(int h, int& u, int& v) {
   }
 }
 
-template <typename R, int TX, int TY, bool PML>
-__global__ __launch_bounds__(256) void k_yee_mid(Tables T, FieldBands Bd) {
+// J: some run has species (else J is zero: not read, not cleared).  NT threads: 256, or 1024
+// where few tiles cover the boxes and their cells' serial chain is what a launch takes.
+template <typename R, int TX, int TY, bool PML, bool J, int NT>
+__global__ __launch_bounds__(NT) void k_yee_mid(Tables T, const RunDesc* out, int64_t* clock_in,
+                                                int64_t* clock_out) {
   constexpr int EW = TX + 3, EH = TY + 3, BW = TX + 2, BH = TY + 2, NC = TX * TY;
   constexpr int LX = Log2<TX>::v;
-  constexpr int PER = (NC + 255) / 256;                    // interior cells per thread
+  constexpr int PER = (NC + NT - 1) / NT;                    // interior cells per thread
   constexpr int ER = EW * EH - NC, BR = BW * BH - NC;      // halo rings of E and B
   constexpr int JR = TX + TY + 1;                          // J outside the tile that E needs
-  constexpr int NER = (ER + 255) / 256, NBR = (BR + 255) / 256, NJR = (JR + 255) / 256;
+  constexpr int NER = (ER + NT - 1) / NT, NBR = (BR + NT - 1) / NT, NJR = (JR + NT - 1) / NT;
   static_assert(TX <= MID_MAX_TX && TY <= MID_MAX_TY, "field tile too large");
   __shared__ R sE[3][EW * EH];
   __shared__ R sB[3][BW * BH];
-  int blk;
-  const int ri = cell_block(T, blk);   // blk: tile of the run (T.run_blk is the tile prefix)
+  // workgroup -> tile (T.run_blk is the tile prefix): XCD x (workgroups x, x + 8, ...) takes
+  // the x-th eighth of the tiles, so that a tile's halo is mostly in its own L2
+  const int vt = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+  if (vt >= T.run_blk[T.nruns]) return;
+  const int ri = uniform(find_owner(T.run_blk, T.nruns, vt));
+  const int blk = uniform(vt - T.run_blk[ri]);   // tile of the run
   const RunDesc& r = run_of(T, ri);
+  const RunDesc& ro = out[ri];
   const int nx = r.nx, ny = r.ny;
-  const int ntx = nx / TX;
-  int tj = blk / ntx, ti = blk - tj * ntx;
-  if (PML && r.pml_cells > 0) {
-    // the tile columns that reach into a layer (ke at each end) come first, so that their
-    // longer work overlaps the interior tiles instead of trailing them
-    const int ke = (r.pml_cells + TX) / TX, nty = ny / TY;
-    if (2 * ke < ntx) {
-      if (blk < 2 * ke * nty) {
-        const int col = blk / nty;
-        tj = blk - col * nty;
-        ti = col < ke ? col : ntx - 2 * ke + col;
-      } else {
-        const int rest = blk - 2 * ke * nty, ncol = ntx - 2 * ke;
-        tj = rest / ncol;
-        ti = ke + rest - tj * ncol;
-      }
-    }
-  }
-  const int tile = tj * ntx + ti;
-  const int a = ti * TX, c = tj * TY;
-  const int64_t tile0 = Bd.tile_pfx[ri];
-  const int cur = *Bd.parity & 1;
-  const R* bin = (const R*)Bd.base + (int64_t)cur * Bd.half;
-  R* bout = (R*)Bd.base + (int64_t)(cur ^ 1) * Bd.half;
-  gptr<R> f[F_NUM];
+  const int sh = mid_shift(r.open_x && r.pml_cells == 0, nx, TX);
+  const int ntx = (nx + sh + TX - 1) / TX;
+  const int tj = blk / ntx, ti = blk - tj * ntx;
+  const int a = ti * TX - sh, c = tj * TY;
+  const int x0 = r.x0;
+  gptr<R> f[9];
 #pragma unroll
-  for (int k = 0; k < F_NUM; ++k) f[k] = gp((R*)r.f[k]);
+  for (int k = 0; k < 9; ++k) f[k] = gp((R*)r.f[k]);
+  // array index of the cell at local (u, v) of the E region: box column a - 1 + u, row c - 1 + v
+  auto at = [&](int u, int v) -> int64_t {
+    int i = wrap_near_box(a - 1 + u, nx) + x0;
+    i = i >= nx ? i - nx : i;
+    return (int64_t)wrap_near_box(c - 1 + v, ny) * nx + i;
+  };
   const int tid = threadIdx.x;
   // the antenna current of this step where a run has one, added to J in the E update
   // exactly as the antenna kernel would have added it to the array (that kernel does not
-  // run before a fused update; the clock advances in the launch that follows).  Column ia
-  // is local column u_ant of the E-update range [a, a + TX] (maybe as the wrapped image of
-  // column 0); it is computed first, per row, while nothing else is live.
+  // run before a fused update; this one advances the clock from its set to the other).
+  // Column ia (or its wrapped image) lies in the E-update range [a, a + TX] of few tiles; the
+  // current is computed first, per row, while nothing else is live.
   __shared__ R sAnt[MID_MAX_TY + 2];
-  int u_ant = -1;
-  if (r.has_laser && Bd.step) {
-    const int ia = array_x(r, r.laser.ia);
-    const int ua = ia >= a && ia <= a + TX ? ia - a + 1 : (ia == 0 && a + TX == nx ? TX + 1 : -1);
+  bool ant = false;
+  if (clock_in) {
+    const int64_t now = *clock_in;
+    if (vt == 0 && tid == 0) *clock_out = now + 1;
+    const int ia = r.laser.ia;
     double jant;
-    const double t_ant = (double)(*Bd.step + 1) * r.dt;
-    if (ua > 0 && antenna_current<2>(r, t_ant, 0, 0, jant)) {   // inside the envelope
-      u_ant = ua;
+    const double t_ant = (double)(now + 1) * r.dt;
+    if (r.has_laser && ((ia >= a && ia <= a + TX) || ia + nx <= a + TX) &&
+        antenna_current<2>(r, t_ant, 0, 0, jant)) {   // inside the envelope
+      ant = true;
       if (tid < TY + 1) {
-        antenna_current<2>(r, t_ant, wrap_once(c + tid, ny), 0, jant);
+        antenna_current<2>(r, t_ant, wrap_near_box(c + tid, ny), 0, jant);
         sAnt[1 + tid] = R(jant);
       }
     }
   }
+  // tile cell q lies in the box
+  auto own = [&](int q) {
+    const int p = a + (q & (TX - 1));
+    return p >= 0 && p < nx && c + (q >> LX) < ny;
+  };
+  // PML layers (lpic_set_pml) in reach of this tile: psi is read from the current half
+  // and, for the tile's own cells, written to the other half at the end (the neighbours
+  // recompute this tile's edge values from the current half during this launch).  A thread's
+  // cells share a column: its slot and coefficients are loaded once, psi with the fields.
+  const bool pml_tile = PML && r.pml_cells > 0 &&
+                        (a - 1 < r.pml_cells || a + TX + 1 > nx - r.pml_cells);
+  const int hcur = r.psi_half;
+  R* psi = (R*)r.psi;
+  static_assert(NT % TX == 0, "a thread's cells share a column");
+  int slot = -1;
+  R cb[3] = {R(0), R(0), R(0)}, ce[3] = {R(0), R(0), R(0)};
+  R ps[PML ? PER : 1][4];
+  if constexpr (PML) {
+    if (pml_tile) slot = pml_slot(r, wrap_near_box(a + (tid & (TX - 1)), nx));
+    if (slot >= 0) {
+      pml_coef<R>(r, true, slot, cb[0], cb[1], cb[2]);
+      pml_coef<R>(r, false, slot, ce[0], ce[1], ce[2]);
+#pragma unroll
+      for (int p = 0; p < PER; ++p) {
+        const int q = tid + p * NT;
+        if (NC % NT == 0 || q < NC) {
+          const int64_t row = wrap_near_box(c + (q >> LX), ny);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) ps[p][k] = psi[pml_index(r, hcur, k, row, slot)];
+        }
+      }
+    }
+  }
   // every load of the workgroup is issued before the first is used: the tile's own E, B
-  // and J, the halo rings from the snapshot, and the J of the column and row past the tile
+  // and J, the halo rings, and the J of the column and row past the tile
   R e[PER][3], b[PER][3], jv[PER][3], er[NER][3], br[NBR][3], je[NJR][3];
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int q = tid + p * 256;
-    if (NC % 256 == 0 || q < NC) {
-      const int64_t g = (int64_t)(c + (q >> LX)) * nx + a + (q & (TX - 1));
+    const int q = tid + p * NT;
+    if (NC % NT == 0 || q < NC) {
+      const int64_t g = at((q & (TX - 1)) + 1, (q >> LX) + 1);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         e[p][k] = f[F_EX + k][g];
         b[p][k] = f[F_BX + k][g];
-        jv[p][k] = f[F_JX + k][g];
+        jv[p][k] = J ? f[F_JX + k][g] : R(0);
       }
     }
   }
 #pragma unroll
   for (int p = 0; p < NER; ++p) {
-    const int h = tid + p * 256;
+    const int h = tid + p * NT;
     if (h < ER) {
       int u, v;
       ring_cell<TX, TY, 2>(h, u, v);
-      const int i = wrap_once(a - 1 + u, nx), j = wrap_once(c - 1 + v, ny);
+      const int64_t g = at(u, v);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) er[p][k] = bin[band_at(Bd, ntx, tile0, i, j, k)];
+      for (int k = 0; k < 3; ++k) er[p][k] = f[F_EX + k][g];
     }
   }
 #pragma unroll
   for (int p = 0; p < NBR; ++p) {
-    const int h = tid + p * 256;
+    const int h = tid + p * NT;
     if (h < BR) {
       int u, v;
       ring_cell<TX, TY, 1>(h, u, v);
-      const int i = wrap_once(a - 1 + u, nx), j = wrap_once(c - 1 + v, ny);
+      const int64_t g = at(u, v);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) br[p][k] = bin[band_at(Bd, ntx, tile0, i, j, 3 + k)];
+      for (int k = 0; k < 3; ++k) br[p][k] = f[F_BX + k][g];
     }
   }
 #pragma unroll
   for (int p = 0; p < NJR; ++p) {
-    const int h = tid + p * 256;
+    const int h = tid + p * NT;
     if (h < JR) {   // column u = TX + 1 (v = 1 .. TY + 1), then row v = TY + 1 (u = 1 .. TX)
       const int u = h <= TY ? TX + 1 : h - TY, v = h <= TY ? 1 + h : TY + 1;
-      const int64_t g = (int64_t)wrap_once(c - 1 + v, ny) * nx + wrap_once(a - 1 + u, nx);
+      const int64_t g = at(u, v);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) je[p][k] = f[F_JX + k][g];
+      for (int k = 0; k < 3; ++k) je[p][k] = J ? f[F_JX + k][g] : R(0);
     }
   }
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int q = tid + p * 256;
-    if (NC % 256 == 0 || q < NC) {
+    const int q = tid + p * NT;
+    if (NC % NT == 0 || q < NC) {
       const int v = (q >> LX) + 1, u = (q & (TX - 1)) + 1;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -475,7 +474,7 @@ __global__ __launch_bounds__(256) void k_yee_mid(Tables T, FieldBands Bd) {
   }
 #pragma unroll
   for (int p = 0; p < NER; ++p) {
-    const int h = tid + p * 256;
+    const int h = tid + p * NT;
     if (h < ER) {
       int u, v;
       ring_cell<TX, TY, 2>(h, u, v);
@@ -485,7 +484,7 @@ __global__ __launch_bounds__(256) void k_yee_mid(Tables T, FieldBands Bd) {
   }
 #pragma unroll
   for (int p = 0; p < NBR; ++p) {
-    const int h = tid + p * 256;
+    const int h = tid + p * NT;
     if (h < BR) {
       int u, v;
       ring_cell<TX, TY, 1>(h, u, v);
@@ -498,39 +497,24 @@ __global__ __launch_bounds__(256) void k_yee_mid(Tables T, FieldBands Bd) {
   const R hx1 = R(h1 / r.dx), hy1 = R(h1 / r.dy);
   const R hx2 = R(h2 / r.dx), hy2 = R(h2 / r.dy), hh2 = R(h2);
   const bool mur = r.open_x != 0 && r.pml_cells == 0;
-  // PML layers (lpic_set_pml) in reach of this tile: psi is read from the current half
-  // and, for the tile's own cells, written to the other half (the neighbours recompute
-  // this tile's edge values from the current half during this launch)
-  const int PL = r.pml_cells;
-  const bool pml_tile = PML && PL > 0 && (a - 1 < PL || a + TX + 1 > nx - PL);
-  const int hcur = pml_tile ? pml_half(r) : 0;
-  R* psi = (R*)r.psi;
-  // 1. B half update on the whole B region (reads E only): the tile's cells (their psi
-  // parked in the other half, where the same thread picks it up for the second B half),
-  // then the ring around it
-  auto b_first = [&](int u, int v, bool own) {
+  // one stretched difference pair of a cell: psi (y, z) advanced, the differences replaced
+  auto stretch = [&](const R* k, R& py, R& pz, R& Dy, R& Dz) {
+    py = k[0] * py + k[1] * Dy;
+    pz = k[0] * pz + k[1] * Dz;
+    Dy = Dy * k[2] + py;
+    Dz = Dz * k[2] + pz;
+  };
+  // 1. B half update on the whole B region (reads E only): the tile's cells (their psi in
+  // registers until the second B half), then the ring around it.  pb2, pb3: psi of By and Bz
+  // and k the coefficients where the column lies in a layer (in)
+  auto b_first = [&](int u, int v, bool in, const R* k, R& pb2, R& pb3) {
     const int ie = v * EW + u, q = v * BW + u, gu = a - 1 + u;
     const R ex = sE[0][ie], ey = sE[1][ie], ez = sE[2][ie];
     const R dbx = -hy1 * (sE[2][ie + EW] - ez);
-    R dby = hx1 * (sE[2][ie + 1] - ez);
-    R dbz = -hx1 * (sE[1][ie + 1] - ey) + hy1 * (sE[0][ie + EW] - ex);
-    if (pml_tile) {
-      const int sl = pml_slot(r, wrap_once(gu, nx));
-      if (sl >= 0) {
-        const int64_t row = wrap_once(c - 1 + v, ny);
-        R pb, pc, ik;
-        pml_coef<R>(r, true, sl, pb, pc, ik);
-        const R Dz = sE[2][ie + 1] - ez, Dy = sE[1][ie + 1] - ey;
-        const R p2 = pb * psi[pml_index(r, hcur, 2, row, sl)] + pc * Dz;
-        const R p3 = pb * psi[pml_index(r, hcur, 3, row, sl)] + pc * Dy;
-        dby = hx1 * (Dz * ik + p2);
-        dbz = -hx1 * (Dy * ik + p3) + hy1 * (sE[0][ie + EW] - ex);
-        if (own) {
-          psi[pml_index(r, hcur ^ 1, 2, row, sl)] = p2;
-          psi[pml_index(r, hcur ^ 1, 3, row, sl)] = p3;
-        }
-      }
-    }
+    R Dz = sE[2][ie + 1] - ez, Dy = sE[1][ie + 1] - ey;
+    if (PML && in) stretch(k, pb2, pb3, Dz, Dy);   // By takes dEz/dx, Bz takes dEy/dx
+    const R dby = hx1 * Dz;
+    const R dbz = -hx1 * Dy + hy1 * (sE[0][ie + EW] - ex);
     sB[0][q] += dbx;
     if (mur && gu == nx - 2 && u + 1 < BW) {   // Mur for column nx-1
       sB[1][q + 1] = mur_edge<R>(sB[1][q + 1], sB[1][q], dby, h1, r.dx, 1);
@@ -543,48 +527,49 @@ __global__ __launch_bounds__(256) void k_yee_mid(Tables T, FieldBands Bd) {
   };
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int q = tid + p * 256;
-    if (NC % 256 == 0 || q < NC) b_first((q & (TX - 1)) + 1, (q >> LX) + 1, true);
+    const int q = tid + p * NT;
+    if (NC % NT == 0 || q < NC)
+      b_first((q & (TX - 1)) + 1, (q >> LX) + 1, slot >= 0, cb, ps[PML ? p : 0][2],
+              ps[PML ? p : 0][3]);
   }
 #pragma unroll
   for (int p = 0; p < NBR; ++p) {
-    const int h = tid + p * 256;
+    const int h = tid + p * NT;
     if (h < BR) {
       int u, v;
       ring_cell<TX, TY, 1>(h, u, v);
-      b_first(u, v, false);
+      R k[3], p2 = R(0), p3 = R(0);
+      const int sl = pml_tile ? pml_slot(r, wrap_near_box(a - 1 + u, nx)) : -1;
+      if (sl >= 0) {
+        const int64_t row = wrap_near_box(c - 1 + v, ny);
+        pml_coef<R>(r, true, sl, k[0], k[1], k[2]);
+        p2 = psi[pml_index(r, hcur, 2, row, sl)];
+        p3 = psi[pml_index(r, hcur, 3, row, sl)];
+      }
+      b_first(u, v, sl >= 0, k, p2, p3);
     }
   }
   __syncthreads();
   // 2. E full update on [a, a+TX+1) x [c, c+TY+1) (reads B): the tile's cells with the J
   // held by their threads, then the column and row past the tile
-  auto e_update = [&](int u, int v, R jx, R jy, R jz, bool own) {
+  auto e_update = [&](int u, int v, R jx, R jy, R jz, bool in, const R* k, R& p0, R& p1) {
     const int ib = v * BW + u, ie = v * EW + u, gu = a - 1 + u;
-    if (u == u_ant) {
+    if (ant && (gu == r.laser.ia || gu - nx == r.laser.ia)) {
       if (r.laser.pol == 1) jy += sAnt[v];
       else jz += sAnt[v];
     }
     const R bx = sB[0][ib], by = sB[1][ib], bz = sB[2][ib];
-    const R dex = hy2 * (bz - sB[2][ib - BW]) - hh2 * jx;
-    R dey = -hx2 * (bz - sB[2][ib - 1]) - hh2 * jy;
-    R dez = hx2 * (by - sB[1][ib - 1]) - hy2 * (bx - sB[0][ib - BW]) - hh2 * jz;
-    if (pml_tile) {   // two merged halves of dt/2: the recursion runs twice
-      const int sl = pml_slot(r, wrap_once(gu, nx));
-      if (sl >= 0) {
-        const int64_t row = wrap_once(c - 1 + v, ny);
-        R pb, pc, ik;
-        pml_coef<R>(r, false, sl, pb, pc, ik);
-        const R Dz = bz - sB[2][ib - 1], Dy = by - sB[1][ib - 1];
-        const R q0 = pb * psi[pml_index(r, hcur, 0, row, sl)] + pc * Dz, q0b = pb * q0 + pc * Dz;
-        const R q1 = pb * psi[pml_index(r, hcur, 1, row, sl)] + pc * Dy, q1b = pb * q1 + pc * Dy;
-        dey = -hx2 * (Dz * ik + R(0.5) * (q0 + q0b)) - hh2 * jy;
-        dez = hx2 * (Dy * ik + R(0.5) * (q1 + q1b)) - hy2 * (bx - sB[0][ib - BW]) - hh2 * jz;
-        if (own) {
-          psi[pml_index(r, hcur ^ 1, 0, row, sl)] = q0b;
-          psi[pml_index(r, hcur ^ 1, 1, row, sl)] = q1b;
-        }
-      }
+    R Dz = bz - sB[2][ib - 1], Dy = by - sB[1][ib - 1];
+    if (PML && in) {   // two merged halves of dt/2: the recursion runs twice
+      const R q0 = k[0] * p0 + k[1] * Dz, q1 = k[0] * p1 + k[1] * Dy;
+      p0 = k[0] * q0 + k[1] * Dz;
+      p1 = k[0] * q1 + k[1] * Dy;
+      Dz = Dz * k[2] + R(0.5) * (q0 + p0);
+      Dy = Dy * k[2] + R(0.5) * (q1 + p1);
     }
+    const R dex = hy2 * (bz - sB[2][ib - BW]) - hh2 * jx;
+    const R dey = -hx2 * Dz - hh2 * jy;
+    const R dez = hx2 * Dy - hy2 * (bx - sB[0][ib - BW]) - hh2 * jz;
     sE[0][ie] += dex;
     if (mur && gu == 1 && u >= 2) {   // Mur for column 0
       sE[1][ie - 1] = mur_edge<R>(sE[1][ie - 1], sE[1][ie], dey, h2, r.dx, 2);
@@ -597,45 +582,41 @@ __global__ __launch_bounds__(256) void k_yee_mid(Tables T, FieldBands Bd) {
   };
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int q = tid + p * 256;
-    if (NC % 256 == 0 || q < NC)
-      e_update((q & (TX - 1)) + 1, (q >> LX) + 1, jv[p][0], jv[p][1], jv[p][2], true);
+    const int q = tid + p * NT;
+    if (NC % NT == 0 || q < NC)
+      e_update((q & (TX - 1)) + 1, (q >> LX) + 1, jv[p][0], jv[p][1], jv[p][2], slot >= 0, ce,
+               ps[PML ? p : 0][0], ps[PML ? p : 0][1]);
   }
 #pragma unroll
   for (int p = 0; p < NJR; ++p) {
-    const int h = tid + p * 256;
-    if (h < JR)
-      e_update(h <= TY ? TX + 1 : h - TY, h <= TY ? 1 + h : TY + 1, je[p][0], je[p][1],
-               je[p][2], false);
+    const int h = tid + p * NT;
+    if (h < JR) {
+      const int u = h <= TY ? TX + 1 : h - TY, v = h <= TY ? 1 + h : TY + 1;
+      R k[3], p0 = R(0), p1 = R(0);
+      const int sl = pml_tile ? pml_slot(r, wrap_near_box(a - 1 + u, nx)) : -1;
+      if (sl >= 0) {
+        const int64_t row = wrap_near_box(c - 1 + v, ny);
+        pml_coef<R>(r, false, sl, k[0], k[1], k[2]);
+        p0 = psi[pml_index(r, hcur, 0, row, sl)];
+        p1 = psi[pml_index(r, hcur, 1, row, sl)];
+      }
+      e_update(u, v, je[p][0], je[p][1], je[p][2], sl >= 0, k, p0, p1);
+    }
   }
   __syncthreads();
   // 3. B half update on the output tile (reads E only)
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int q = tid + p * 256;
-    if (NC % 256 == 0 || q < NC) {
+    const int q = tid + p * NT;
+    if (NC % NT == 0 || q < NC) {
       const int v = (q >> LX) + 1, u = (q & (TX - 1)) + 1;
       const int ie = v * EW + u, ib = v * BW + u, gu = a - 1 + u;
       const R ex = sE[0][ie], ey = sE[1][ie], ez = sE[2][ie];
       const R dbx = -hy1 * (sE[2][ie + EW] - ez);
-      R dby = hx1 * (sE[2][ie + 1] - ez);
-      R dbz = -hx1 * (sE[1][ie + 1] - ey) + hy1 * (sE[0][ie + EW] - ex);
-      if (pml_tile) {
-        const int sl = pml_slot(r, wrap_once(gu, nx));
-        if (sl >= 0) {
-          const int64_t row = c - 1 + v;
-          R pb, pc, ik;
-          pml_coef<R>(r, true, sl, pb, pc, ik);
-          const R Dz = sE[2][ie + 1] - ez, Dy = sE[1][ie + 1] - ey;
-          R* q2 = psi + pml_index(r, hcur ^ 1, 2, row, sl);
-          R* q3 = psi + pml_index(r, hcur ^ 1, 3, row, sl);
-          const R p2 = pb * *q2 + pc * Dz, p3 = pb * *q3 + pc * Dy;
-          dby = hx1 * (Dz * ik + p2);
-          dbz = -hx1 * (Dy * ik + p3) + hy1 * (sE[0][ie + EW] - ex);
-          *q2 = p2;
-          *q3 = p3;
-        }
-      }
+      R Dz = sE[2][ie + 1] - ez, Dy = sE[1][ie + 1] - ey;
+      if (PML && slot >= 0) stretch(cb, ps[PML ? p : 0][2], ps[PML ? p : 0][3], Dz, Dy);
+      const R dby = hx1 * Dz;
+      const R dbz = -hx1 * Dy + hy1 * (sE[0][ie + EW] - ex);
       sB[0][ib] += dbx;
       if (mur && gu == nx - 2 && u + 1 <= TX) {   // Mur for column nx-1
         sB[1][ib + 1] = mur_edge<R>(sB[1][ib + 1], sB[1][ib], dby, h1, r.dx, 1);
@@ -648,35 +629,33 @@ __global__ __launch_bounds__(256) void k_yee_mid(Tables T, FieldBands Bd) {
     }
   }
   __syncthreads();
-  // 4. the tile's E and B to the arrays, its edges to the other snapshot
-  const int64_t bbase = (tile0 + tile) * 6 * (3 * (TX + TY));
+  // 4. the tile's E and B to the other set, its J there cleared
+  gptr<R> o[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) o[k] = gp((R*)ro.f[k]);
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int q = tid + p * 256;
-    if (NC % 256 == 0 || q < NC) {
+    const int q = tid + p * NT;
+    if ((NC % NT == 0 || q < NC) && own(q)) {
       const int lj = q >> LX, li = q & (TX - 1);
       const int ie = (lj + 1) * EW + li + 1, ib = (lj + 1) * BW + li + 1;
-      const int64_t g = (int64_t)(c + lj) * nx + a + li;
+      const int64_t g = at(li + 1, lj + 1);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        f[F_EX + k][g] = sE[k][ie];
-        f[F_BX + k][g] = sB[k][ib];
+        o[F_EX + k][g] = sE[k][ie];
+        o[F_BX + k][g] = sB[k][ib];
+        if (J) o[F_JX + k][g] = R(0);
       }
-      if (band_col(li, TX) >= 0 || band_col(lj, TY) >= 0) {
+      if (PML && slot >= 0) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          band_put(bout, Bd, bbase, li, lj, k, sE[k][ie]);
-          band_put(bout, Bd, bbase, li, lj, 3 + k, sB[k][ib]);
-        }
+        for (int k = 0; k < 4; ++k) psi[pml_index(r, hcur ^ 1, k, c + lj, slot)] = ps[PML ? p : 0][k];
       }
     }
   }
 }
 
-// J := 0 (and the charge arrays when asked and present), four cells per thread, 256 cells
-// per wave, four waves per workgroup.  flip != NULL: the launch follows a fused field update; its first
-// thread makes the snapshot that update wrote the present one and, with clock != NULL,
-// advances the antenna clock as the antenna kernel would have.
+// The charge arrays a step accumulates := 0, four cells per thread, 256 cells per wave, four
+// waves per workgroup (the steps whose J a fused field update cleared).
 template <typename R>
 __device__ __forceinline__ void zero4(R* p, int64_t c, int64_t n) {
   if (c + 3 < n && ((uintptr_t)p & 15) == 0) {
@@ -692,12 +671,7 @@ __device__ __forceinline__ void zero4(R* p, int64_t c, int64_t n) {
 }
 
 template <typename R, int DIM>
-__global__ __launch_bounds__(256) void k_clear_sources(Tables T, int nblk, int with_rho,
-                                                       int32_t* flip, int64_t* clock) {
-  if (flip && blockIdx.x == 0 && threadIdx.x == 0) {
-    *flip ^= 1;
-    if (clock) *clock += 1;
-  }
+__global__ __launch_bounds__(256) void k_clear_charge(Tables T, int nblk, int with_rho) {
   // each wave clears one 256-cell block of the cell-block prefix (four per workgroup)
   const int vb = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   if (vb >= nblk) return;
@@ -710,9 +684,6 @@ __global__ __launch_bounds__(256) void k_clear_sources(Tables T, int nblk, int w
   const int64_t n = (int64_t)r.nx * r.ny * (DIM == 3 ? r.nz : 1);
   const int64_t c = (int64_t)blk * 256 + 4 * (threadIdx.x & 63);
   if (c >= n) return;
-  zero4((R*)r.f[F_JX], c, n);
-  zero4((R*)r.f[F_JY], c, n);
-  zero4((R*)r.f[F_JZ], c, n);
   // with_rho: 1 both charge arrays, 3 rho0 only, 4 rho1 only (as k_yee_e's zero_j)
   if ((with_rho == 1 || with_rho == 3) && r.f[F_R0]) zero4((R*)r.f[F_R0], c, n);
   if ((with_rho == 1 || with_rho == 4) && r.f[F_R1]) zero4((R*)r.f[F_R1], c, n);
@@ -2069,11 +2040,13 @@ __global__ __launch_bounds__(256) void k_window_kill(Tables T, int run, int m) {
   }
 }
 
-__global__ void k_window_advance(Tables T, int run, int m) {
+__global__ void k_window_advance(Tables T, RunDesc* other, int run, int m) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     RunDesc* r = const_cast<RunDesc*>(&T.runs[run]);
-    const int x0 = r->x0 + m;
-    r->x0 = x0 >= r->nx ? x0 - r->nx : x0;
+    int x0 = r->x0 + m;
+    x0 = x0 >= r->nx ? x0 - r->nx : x0;
+    r->x0 = x0;
+    if (other) other[run].x0 = x0;
   }
 }
 
@@ -2198,58 +2171,71 @@ __global__ __launch_bounds__(256) void k_store_positions(Tables T, double* x, do
 // =======================================================================================
 // Host-side launchers
 // =======================================================================================
-template <typename R, int DIM>
-static void launch_yee_t(const Tables& T, int nblocks, int which, double frac, int zero_j,
-                         int halves, hipStream_t st, const FieldBands& bands) {
-  if (which == 0) k_yee_e<R, DIM><<<nblocks, 256, 0, st>>>(T, frac, zero_j, halves);
-  else k_yee_b<R, DIM><<<nblocks, 256, 0, st>>>(T, frac, bands);
-}
-
 void launch_yee(const Tables& T, int prec, int dim, int nblocks, int which, double frac,
-                int zero_j, int halves, hipStream_t st, const FieldBands* bands) {
-  FieldBands nb;
-  memset(&nb, 0, sizeof(nb));
-  const FieldBands& b = (bands && dim == 2) ? *bands : nb;
-  if (prec == 0) {
-    if (dim == 2) launch_yee_t<float, 2>(T, nblocks, which, frac, zero_j, halves, st, b);
-    else launch_yee_t<float, 3>(T, nblocks, which, frac, zero_j, halves, st, b);
+                int zero_j, int halves, hipStream_t st, const RunDesc* out, int64_t* clock) {
+  if (out) {   // 2D simulations only
+    if (which == 0 && prec == 0) k_yee_e<float, 2, true><<<nblocks, 256, 0, st>>>(T, frac, zero_j, halves, out, clock);
+    else if (which == 0) k_yee_e<double, 2, true><<<nblocks, 256, 0, st>>>(T, frac, zero_j, halves, out, clock);
+    else if (prec == 0) k_yee_b<float, 2, true><<<nblocks, 256, 0, st>>>(T, frac, out);
+    else k_yee_b<double, 2, true><<<nblocks, 256, 0, st>>>(T, frac, out);
+  } else if (which == 0) {
+    LPIC_PD(prec, dim, (k_yee_e<R, D, false><<<nblocks, 256, 0, st>>>(T, frac, zero_j, halves, nullptr, nullptr)));
   } else {
-    if (dim == 2) launch_yee_t<double, 2>(T, nblocks, which, frac, zero_j, halves, st, b);
-    else launch_yee_t<double, 3>(T, nblocks, which, frac, zero_j, halves, st, b);
+    LPIC_PD(prec, dim, (k_yee_b<R, D, false><<<nblocks, 256, 0, st>>>(T, frac, nullptr)));
   }
 }
 
+// Tiles up to which a 64 x 16 tile takes 1024 threads: below two tiles a CU the four cells
+// that a thread of 256 handles one after the other are what a launch waits for.
+constexpr int MID_FEW_TILES = 256;
+
+template <typename R, int TX, int TY, bool PML, bool J>
+static void launch_yee_mid_j(const Tables& T, int ntiles, const FieldSets& b, hipStream_t st) {
+  const int grid = (ntiles + 7) / 8 * 8;
+  if constexpr (TX * TY >= 1024)
+    if (ntiles <= MID_FEW_TILES) {
+      k_yee_mid<R, TX, TY, PML, J, 1024><<<grid, 1024, 0, st>>>(T, b.out, b.clock_in, b.clock_out);
+      return;
+    }
+  k_yee_mid<R, TX, TY, PML, J, 256><<<grid, 256, 0, st>>>(T, b.out, b.clock_in, b.clock_out);
+}
+
 template <typename R, int TX, bool PML>
-static void launch_yee_mid_t(const Tables& T, int ntiles, const FieldBands& b, hipStream_t st) {
-  if (b.ty == 16) k_yee_mid<R, TX, 16, PML><<<ntiles, 256, 0, st>>>(T, b);
-  else if (b.ty == 8) k_yee_mid<R, TX, 8, PML><<<ntiles, 256, 0, st>>>(T, b);
-  else k_yee_mid<R, TX, 4, PML><<<ntiles, 256, 0, st>>>(T, b);
+static void launch_yee_mid_t(const Tables& T, int ntiles, const FieldSets& b, hipStream_t st) {
+#define LPIC_MID(ty)                                                       \
+  do {                                                                     \
+    if (b.species) launch_yee_mid_j<R, TX, ty, PML, true>(T, ntiles, b, st); \
+    else launch_yee_mid_j<R, TX, ty, PML, false>(T, ntiles, b, st);        \
+  } while (0)
+  if (b.ty == 16) LPIC_MID(16);
+  else if (b.ty == 8) LPIC_MID(8);
+  else LPIC_MID(4);
+#undef LPIC_MID
 }
 
 template <typename R, bool PML>
-static void launch_yee_mid_r(const Tables& T, int ntiles, const FieldBands& b, hipStream_t st) {
+static void launch_yee_mid_r(const Tables& T, int ntiles, const FieldSets& b, hipStream_t st) {
   if (b.tx == 64) launch_yee_mid_t<R, 64, PML>(T, ntiles, b, st);
   else if (b.tx == 32) launch_yee_mid_t<R, 32, PML>(T, ntiles, b, st);
   else if (b.tx == 16) launch_yee_mid_t<R, 16, PML>(T, ntiles, b, st);
   else launch_yee_mid_t<R, 8, PML>(T, ntiles, b, st);
 }
 
-void launch_yee_mid(const Tables& T, int prec, int ntiles, const FieldBands& bands, bool pml,
+void launch_yee_mid(const Tables& T, int prec, int ntiles, const FieldSets& sets, bool pml,
                     hipStream_t st) {
   if (ntiles <= 0) return;
   if (prec == 0) {
-    if (pml) launch_yee_mid_r<float, true>(T, ntiles, bands, st);
-    else launch_yee_mid_r<float, false>(T, ntiles, bands, st);
+    if (pml) launch_yee_mid_r<float, true>(T, ntiles, sets, st);
+    else launch_yee_mid_r<float, false>(T, ntiles, sets, st);
   } else {
-    if (pml) launch_yee_mid_r<double, true>(T, ntiles, bands, st);
-    else launch_yee_mid_r<double, false>(T, ntiles, bands, st);
+    if (pml) launch_yee_mid_r<double, true>(T, ntiles, sets, st);
+    else launch_yee_mid_r<double, false>(T, ntiles, sets, st);
   }
 }
 
-void launch_clear_sources(const Tables& T, int prec, int dim, int nblocks, int with_rho,
-                          int32_t* flip, int64_t* clock, hipStream_t st) {
-  LPIC_PD(prec, dim, (k_clear_sources<R, D><<<(nblocks + 3) / 4, 256, 0, st>>>(T, nblocks, with_rho,
-                                                                              flip, clock)));
+void launch_clear_charge(const Tables& T, int prec, int dim, int nblocks, int with_rho,
+                         hipStream_t st) {
+  LPIC_PD(prec, dim, (k_clear_charge<R, D><<<(nblocks + 3) / 4, 256, 0, st>>>(T, nblocks, with_rho)));
 }
 
 void launch_laser(const Tables& T, int prec, int dim, int nruns, int bpr, double t,
@@ -2366,14 +2352,14 @@ void launch_diag_clear(const Tables& T, int nruns, hipStream_t st) {
   k_diag_clear<<<nruns, 64, 0, st>>>(T);
 }
 
-void launch_window_shift(const Tables& T, int prec, int dim, int run, int m, int64_t rows,
-                         int nblk_part, hipStream_t st) {
+void launch_window_shift(const Tables& T, RunDesc* other, int prec, int dim, int run, int m,
+                         int64_t rows, int nblk_part, hipStream_t st) {
   const unsigned nb = (unsigned)((rows * m + 255) / 256);
   if (prec == 0) k_window_clear<float><<<nb, 256, 0, st>>>(T, run, m);
   else k_window_clear<double><<<nb, 256, 0, st>>>(T, run, m);
   if (nblk_part > 0)
     LPIC_PD(prec, dim, (k_window_kill<R, D><<<nblk_part, 256, 0, st>>>(T, run, m)));
-  k_window_advance<<<1, 64, 0, st>>>(T, run, m);
+  k_window_advance<<<1, 64, 0, st>>>(T, other, run, m);
 }
 
 void launch_window_inject(const Tables& T, int prec, int dim, int seg, int m, int64_t count,
