@@ -2,8 +2,10 @@
 // Boris push + Esirkepov deposit in one pass over a tile-sorted particle stream, with the
 // field tile staged in LDS and the tile's current accumulated in LDS (64-bit fixed point on
 // the FP32 path, FP64 on the FP64 path) before one global atomic flush per non-zero entry;
-// plus the kernel that handles, through global memory, the particles whose stencils have
-// left the staged region of their tile.
+// the particles whose stencils have left the staged region of their tile are pushed through
+// global memory by the workgroup that met them, or, re-binned, by a second pass.
+#include <algorithm>
+
 #include "lpic_internal.hpp"
 
 namespace lpic {
@@ -196,6 +198,62 @@ struct PassList {
   const void* rec;
 };
 
+// An escaped particle: the same push through global memory, and the path it deposits.
+template <typename R>
+struct EscPath {
+  int c[3];
+  R o[3], e[3];
+  R w, vz;
+  int rho;
+};
+
+template <typename R, int DIM, int ORDER>
+__device__ __forceinline__ bool escape_push(const RunDesc& r, const SegDesc& s, int64_t p,
+                                            const PushConst<R>& k, int with_rho, EscPath<R>& d,
+                                            double& ke) {
+  PState<R> ps;
+  load_particle<R, DIM>(s, r, p, ps);
+  if (!ps.alive) return false;
+  const GlobalAcc<R> G = global_acc<R>(r);
+  R x1[3], g1;
+  push<DIM, ORDER>(G, ps.c, ps, k, d.c, d.o, d.e, x1, d.vz, g1);
+  const int n[3] = {r.nx, r.ny, r.nz};
+#pragma unroll
+  for (int i = 0; i < DIM; ++i) {
+    d.c[i] = wrapi(d.c[i], n[i]);
+    advance_cell<R>(ps.c[i], ps.o[i], x1[i], n[i]);
+  }
+  if (leaves_box(r, ps.c[0])) ps.alive = false;
+  store_particle<R, DIM>(s, r, p, ps);
+  d.w = ps.w;
+  d.rho = with_rho == 2 && !ps.alive ? 0 : with_rho;
+  if (ps.alive) {
+    const double u2 = (double)ps.u[0] * ps.u[0] + (double)ps.u[1] * ps.u[1] + (double)ps.u[2] * ps.u[2];
+    ke += (double)ps.w * s.m * u2 / (1.0 + (double)g1);
+  }
+  return true;
+}
+
+// Where a workgroup's escaped particles go.
+//   KEEP (2D simulations of up to FUSED_KEEP slots, without the re-binned path): the
+//     workgroup keeps them itself, at items[base ...] -- the list positions of the particles
+//     it is pushing, so no other workgroup writes there and there is room for all of them --
+//     and pushes them when its tile or species changes (drain_escapes).  A launch over a
+//     list takes 6 us with its gap, whatever it holds: 20 steps of 65,536 FP64 particles
+//     765 us with one and 703 without.
+//   Otherwise the shared list; in 2D through one in LDS (list, cap entries), so that the
+//     particles of a tile reach it side by side and share a deposit box in k_escape.  Where a
+//     tile loses most of its particles (a wake's bubble) the workgroup that meets them is no
+//     place to push them: the last one ends long after the others (14.3 ms for 20 steps of
+//     the 8192 x 512 wakefield box against 13.6).
+struct EscapeOut {
+  EscapeList list;
+  int32_t* count;              // LDS: entries kept, or in the LDS list
+  unsigned long long* lds;     // the LDS list (2D without KEEP): segment << 32 | slot
+  int cap;
+  int64_t base;                // KEEP
+};
+
 // Append the lanes that want it to the escape list (one reservation per wave), with their
 // escape records when the list keeps them (3D only: the 2D body has no registers to spare
 // for the record's words, and 2D particles rarely leave their regions).
@@ -213,14 +271,29 @@ __device__ __forceinline__ void escape_record(const EscapeList& esc, int64_t k,
                     : s.bin_base + r.ntiles;
 }
 
-template <typename R, int DIM>
-__device__ __forceinline__ void escape_append(const EscapeList& esc, bool want, int seg,
+template <typename R, int DIM, bool KEEP>
+__device__ __forceinline__ void escape_append(const EscapeOut& out, bool want, int seg,
                                               int32_t p, const PartPtrs<R>& q,
                                               const RunDesc& r, const SegDesc& s) {
-  const uint64_t mask = __ballot(want);
+  uint64_t mask = __ballot(want);
   if (!mask) return;
+  const EscapeList& esc = out.list;
   const int lane = __lane_id();
-  const int leader = __ffsll((unsigned long long)mask) - 1;
+  int leader = __ffsll((unsigned long long)mask) - 1;
+  if constexpr (DIM == 2) {
+    int k = 0;
+    if (lane == leader) k = atomicAdd(out.count, __popcll(mask));
+    k = __shfl(k, leader, 64) + __popcll(mask & ((1ull << lane) - 1ull));
+    if constexpr (KEEP) {
+      if (want) gp(esc.items)[out.base + k] = (unsigned long long)(uint32_t)p;
+      return;
+    }
+    if (want && k < out.cap) out.lds[k] = ((unsigned long long)seg << 32) | (unsigned long long)p;
+    want = want && k >= out.cap;   // a full LDS list: straight to the shared one
+    mask = __ballot(want);
+    if (!mask) return;
+    leader = __ffsll((unsigned long long)mask) - 1;
+  }
   unsigned int base = 0;
   if (lane == leader) base = atomicAdd(esc.count, (unsigned int)__popcll(mask));
   base = __shfl(base, leader, 64);
@@ -345,7 +418,8 @@ __device__ __forceinline__ bool push_on_chip(const RunDesc& r, const Region& g, 
 template <typename R, int DIM, int ORDER, class LA>
 __device__ __forceinline__ double process_chunk_compact(
     const RunDesc& r, const SegDesc& s, int seg, const Chunk& ch, const Region& g, const LA& L,
-    int with_rho, bool want_ke, const EscapeList& esc, const PassList& pl, int32_t* cbuf) {
+    int with_rho, bool want_ke, const EscapeOut& out, const PassList& pl, int32_t* cbuf) {
+  const EscapeList& esc = out.list;
   const int n[3] = {r.nx, r.ny, r.nz};
   const PushConst<R> k = push_const<R>(r, s);
   const PartPtrs<R> q = part_ptrs<R>(s, r);
@@ -419,23 +493,23 @@ __device__ __forceinline__ double process_chunk_compact(
       late = !push_on_chip<R, DIM, ORDER>(r, g, L, n, b, ps, k, q, p, with_rho, want_ke, ke,
                                           true);
     }
-    escape_append<R, DIM>(esc, late, seg, p, q, r, s);
+    escape_append<R, DIM, false>(out, late, seg, p, q, r, s);
   }
   return ke * s.m;
 }
 
-template <typename R, int DIM, int ORDER, bool DIRECT, class LA>
+template <typename R, int DIM, int ORDER, bool DIRECT, bool KEEP, class LA>
 __device__ __forceinline__ double process_chunk(const RunDesc& r, const SegDesc& s, int seg,
                                                 const Chunk& ch, const Region& g,
                                                 const LA& L, int with_rho,
-                                                bool want_ke, const EscapeList& esc,
+                                                bool want_ke, const EscapeOut& out,
                                                 const PassList& pl, int32_t* cbuf) {
   // 3D: compacted rounds, except for the second pass of the re-binned path on the two-per-CU
   // geometry (DIRECT), whose particles lie inside their present tile (nearly all on chip):
   // there the records are loaded directly, one memory latency and no barriers per round
   if constexpr (DIM == 3)
     if (!(DIRECT && pl.rec))
-      return process_chunk_compact<R, DIM, ORDER>(r, s, seg, ch, g, L, with_rho, want_ke, esc,
+      return process_chunk_compact<R, DIM, ORDER>(r, s, seg, ch, g, L, with_rho, want_ke, out,
                                                   pl, cbuf);
   (void)cbuf;
   const int n[3] = {r.nx, r.ny, r.nz};
@@ -473,10 +547,57 @@ __device__ __forceinline__ double process_chunk(const RunDesc& r, const SegDesc&
       if (in)
         done = push_on_chip<R, DIM, ORDER>(r, g, L, n, a, ps[b], k, q, pi[b], with_rho,
                                            want_ke, ke, check);
-      escape_append<R, DIM>(esc, live && !done, seg, pi[b], q, r, s);
+      escape_append<R, DIM, KEEP>(out, live && !done, seg, pi[b], q, r, s);
     }
   }
   return ke * s.m;
+}
+
+// Empties the workgroup's list at the end of a tile (KEEP: of a tile's species): KEEP pushes
+// the particles (their kinetic energy is returned), otherwise they move to the shared list in
+// one piece.
+// Every thread calls it; the first barrier stands whatever the count.
+template <typename R, int DIM, bool KEEP>
+__device__ __forceinline__ double drain_escapes(const Tables& T, int seg, const EscapeOut& out,
+                                                int with_rho) {
+  __syncthreads();
+  if constexpr (DIM == 3) return 0.0;
+  const int n = *out.count;
+  if (n == 0) return 0.0;
+  double ke = 0.0;
+  if constexpr (KEEP) {
+    const SegDesc& s = seg_of(T, seg);
+    const RunDesc& r = run_of(T, s.run);
+    const PushConst<R> k = push_const<R>(r, s);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+      const int64_t p = (int64_t)gp(out.list.items)[out.base + i];
+      EscPath<R> d;
+      const bool live = s.order == 1 ? escape_push<R, DIM, 1>(r, s, p, k, with_rho, d, ke)
+                                     : escape_push<R, DIM, 2>(r, s, p, k, with_rho, d, ke);
+      if (!live) continue;
+      const GlobalAcc<R> G = global_acc<R>(r);
+      if (s.order == 1) deposit<DIM, 1>(G, d.c, d.o, d.e, d.w, d.vz, k, d.rho);
+      else deposit<DIM, 2>(G, d.c, d.o, d.e, d.w, d.vz, k, d.rho);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      *out.count = 0;
+      atomicAdd(out.list.total, (unsigned long long)n);
+    }
+  } else {
+    const int m = min(n, out.cap);
+    __syncthreads();
+    if (threadIdx.x == 0) *out.count = (int32_t)atomicAdd(out.list.count, (unsigned int)m);
+    __syncthreads();
+    const int64_t base = (int64_t)(uint32_t)*out.count;
+    for (int i = threadIdx.x; i < m; i += blockDim.x)
+      if (base + i < out.list.capacity)
+        gp(out.list.items)[base + i] = out.lds[i];
+    __syncthreads();
+    if (threadIdx.x == 0) *out.count = 0;
+  }
+  __syncthreads();
+  return ke;
 }
 
 template <typename T>
@@ -513,14 +634,15 @@ __device__ __forceinline__ D uniform_copy(const D& src) {
 // split into equal contiguous slices per workgroup.  Consecutive chunks of one tile (and of
 // the other species of the same box, which follow in the table) reuse the staged region;
 // the region is flushed when the tile changes.
-template <typename R, int DIM, int G>
+template <typename R, int DIM, int G, bool KEEP>
 __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_waves_per_eu(fused_waves<R, DIM, G>()))) void k_fused(Tables T, const Chunk* chunks,
                                                const int32_t* nchunks, int with_rho,
                                                double* kinetic, int ke_to_diag,
-                                               EscapeList esc, const int32_t* jshift,
-                                               PassList pl) {
+                                               EscapeList esc, int list_end,
+                                               const int32_t* jshift, PassList pl) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double red[fused_block<R, DIM, G>() / 64];
+  __shared__ int32_t kept;   // escaped particles of the present tile and species (2D)
   R* sm = (R*)smem_raw;
   const int nch = uniform(*nchunks);
   const int nb8 = gridDim.x >> 3;
@@ -547,7 +669,8 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
   // the current planes follow the six field planes; 6 plane values of 4 or 8 bytes end on an
   // 8-byte boundary, as the 64-bit LDS atomics need
   double* jm = (double*)(sm + 6 * plane);
-  // 3D: the round compaction's slot list after the current (and charge) planes
+  // after the current (and charge) planes: 3D the round compaction's slot list, 2D the
+  // list of escaped particles
   int32_t* cbuf = (int32_t*)(jm + (size_t)njplanes * plane);
   LdsAcc<R, ST, DIM == 2> L;
   L.fbase = sm;
@@ -555,7 +678,10 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
   L.st = st;
   L.jfold = 1.0f;
 
-  int cur_run = -1, cur_tile = -1;
+  // (2D: the LDS list takes the launch's LDS after the current planes, up to list_end)
+  EscapeOut out{esc, &kept, (unsigned long long*)cbuf, (list_end - (int)((unsigned char*)cbuf - smem_raw)) / 8, 0};
+  if (threadIdx.x == 0) kept = 0;   // (staging's barrier comes before the first append)
+  int cur_run = -1, cur_tile = -1, cur_seg = -1;
   Region g;
   double ke = 0.0;
   double unscale = 1.0;
@@ -566,10 +692,15 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
     ch.beg = uniform(ch.beg);
     ch.end = uniform(ch.end);
     const SegDesc s = uniform_copy(seg_of(T, ch.seg));
-    if (s.run != cur_run || ch.tile != cur_tile) {
+    const bool new_tile = s.run != cur_run || ch.tile != cur_tile;
+    if (new_tile || (KEEP && ch.seg != cur_seg)) {
+      if (cur_run >= 0) ke += drain_escapes<R, DIM, KEEP>(T, cur_seg, out, with_rho);
+      if (KEEP) out.base = s.pbase + ch.beg;
+      cur_seg = ch.seg;
+    }
+    if (new_tile) {
       if (cur_run >= 0) {
         const RunDesc& rp = run_of(T, cur_run);
-        __syncthreads();
         flush_region<R>(rp, g, st, njplanes, jm, unscale, with_rho);
         if (kinetic || ke_to_diag) {
           const double t = block_sum(ke, red);
@@ -593,11 +724,11 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
     const RunDesc r = run_of(T, s.run);
     const bool want_ke = kinetic || ke_to_diag;
     ke += s.order == 1
-              ? process_chunk<R, DIM, 1, (G >= 7)>(r, s, ch.seg, ch, g, L, with_rho, want_ke, esc, pl, cbuf)
-              : process_chunk<R, DIM, 2, (G >= 7)>(r, s, ch.seg, ch, g, L, with_rho, want_ke, esc, pl, cbuf);
+              ? process_chunk<R, DIM, 1, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf)
+              : process_chunk<R, DIM, 2, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf);
   }
   const RunDesc& rl = run_of(T, cur_run);
-  __syncthreads();
+  ke += drain_escapes<R, DIM, KEEP>(T, cur_seg, out, with_rho);
   flush_region<R>(rl, g, st, njplanes, jm, unscale, with_rho);
   if (kinetic || ke_to_diag) {
     const double t = block_sum(ke, red);
@@ -605,48 +736,116 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
   }
 }
 
-// Escaped particles: the same push and deposit through global memory.  The last workgroup
-// to finish clears the list for the next step.
-template <typename R, int DIM, int ORDER>
-__device__ __forceinline__ double escape_one(const RunDesc& r, const SegDesc& s, int64_t p,
-                                             int with_rho) {
-  PState<R> ps;
-  load_particle<R, DIM>(s, r, p, ps);
-  if (!ps.alive) return 0.0;
-  const GlobalAcc<R> G = global_acc<R>(r);
-  const PushConst<R> k = push_const<R>(r, s);
-  int pcell[3];
-  R po[3], pe[3], x1[3], vz1, g1;
-  push<DIM, ORDER>(G, ps.c, ps, k, pcell, po, pe, x1, vz1, g1);
-  const int n[3] = {r.nx, r.ny, r.nz};
-#pragma unroll
-  for (int d = 0; d < DIM; ++d) advance_cell<R>(ps.c[d], ps.o[d], x1[d], n[d]);
-  if (leaves_box(r, ps.c[0])) ps.alive = false;
-  deposit<DIM, ORDER>(G, pcell, po, pe, ps.w, vz1, k, with_rho == 2 && !ps.alive ? 0 : with_rho);
-  store_particle<R, DIM>(s, r, p, ps);
-  if (!ps.alive) return 0.0;
-  const double u2 = (double)ps.u[0] * ps.u[0] + (double)ps.u[1] * ps.u[1] + (double)ps.u[2] * ps.u[2];
-  return (double)ps.w * s.m * u2 / (1.0 + (double)g1);
-}
-
-// skip_at: a list of at least this many entries was taken by the re-binned path; only the
-// clearing is left to do.
+// Escaped particles of a shared list.  Entries that lie side by side come from one tile and
+// its neighbourhood (escape_append), so a workgroup adds the windows of 256 of them in a box
+// in LDS (pick_box) and flushes it once: with an atomic per window entry the atomics were
+// what a launch took, whatever the number of workgroups (hot slab of 1.5M FP64 particles,
+// 20 steps late in the run: 5.0 ms with 128 workgroups and 5.2 with 1024, 3.8 with boxes).  Each workgroup takes a
+// contiguous share of the list.  skip_at: a list of at least this many entries was taken by
+// the re-binned path; only the clearing is left to do.
 template <typename R, int DIM>
 __global__ __launch_bounds__(256) void k_escape(Tables T, int with_rho, double* kinetic,
-                                                int ke_to_diag, EscapeList esc, int skip_at) {
-  unsigned int cnt = min((int64_t)esc.count[0], esc.capacity);
+                                                int ke_to_diag, EscapeList esc, int skip_at,
+                                                int cap) {
+  extern __shared__ double jm[];
+  __shared__ int red[4][13];
+  __shared__ int wrun[4];
+  int64_t cnt = min((int64_t)esc.count[0], esc.capacity);
   if ((int)min(esc.count[0], 0x7fffffffu) >= skip_at) cnt = 0;
-  for (unsigned int i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt;
-       i += gridDim.x * blockDim.x) {
-    const unsigned long long v = esc.items[i];
-    const int seg = (int)(v >> 32);
-    const int64_t p = (int64_t)(v & 0xffffffffull);
-    const SegDesc& s = seg_of(T, seg);
-    const RunDesc& r = run_of(T, s.run);
-    const double ke = s.order == 1 ? escape_one<R, DIM, 1>(r, s, p, with_rho)
-                                   : escape_one<R, DIM, 2>(r, s, p, with_rho);
-    if (kinetic || ke_to_diag) atomic_add_global(ke_to_diag ? r.diag + DIAG_UKIN : kinetic, ke);
+  const int lane = (int)__lane_id(), wave = (int)(threadIdx.x >> 6);
+  const int planes = 3 + charge_planes(with_rho);
+  // a short list is dealt out to all workgroups one entry at a time and deposits straight
+  // into memory: a box's clearing, bounds and flush would be most of its time
+  const bool few = cnt <= (int64_t)gridDim.x * ESCAPE_FEW;
+  const int64_t passes = (cnt + 255) / 256, per = (passes + gridDim.x - 1) / gridDim.x;
+  const int64_t it0 = few ? 0 : blockIdx.x * per, it1 = few ? 1 : min(it0 + per, passes);
+  NodeBox box;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) { box.at[d] = 0; box.lo[d] = 0; box.ext[d] = 1; }
+  int brun = -1;                  // the box's run
+  for (int64_t it = it0; it < it1; ++it) {
+    const int64_t i = few ? blockIdx.x + (int64_t)gridDim.x * threadIdx.x : it * 256 + 4 * lane + wave;
+    int seg = 0, run = 0;
+    bool live = false;
+    EscPath<R> d;
+    double ke = 0.0;
+    if (i < cnt) {
+      const unsigned long long v = esc.items[i];
+      seg = (int)(v >> 32);
+      const int64_t p = (int64_t)(v & 0xffffffffull);
+      const SegDesc& s = seg_of(T, seg);
+      run = s.run;
+      const RunDesc& r = run_of(T, run);
+      const PushConst<R> k = push_const<R>(r, s);
+      live = s.order == 1 ? escape_push<R, DIM, 1>(r, s, p, k, with_rho, d, ke)
+                          : escape_push<R, DIM, 2>(r, s, p, k, with_rho, d, ke);
+    }
+    if (kinetic || ke_to_diag) {
+      const int first = uniform(run);   // (the first lane's run; the others may differ)
+      if (kinetic || __ballot(run != first) == 0) {
+        ke = wave_sum(ke);
+        if (lane == 0) atomic_add_global(kinetic ? kinetic : run_of(T, first).diag + DIAG_UKIN, ke);
+      } else if (live) {
+        atomic_add_global(run_of(T, run).diag + DIAG_UKIN, ke);
+      }
+    }
+    int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0}, v[3] = {0, 0, 0};
+    bool in = live && run == brun;
+    if (live) {
+      const RunDesc& r = run_of(T, run);
+      const int n[3] = {r.nx, r.ny, r.nz};
+      const bool cic = seg_of(T, seg).order == 1;
+#pragma unroll
+      for (int x = 0; x < DIM; ++x) {
+        if (cic) path_nodes<1>(d.o[x], d.e[x], lo[x], hi[x]);
+        else path_nodes<2>(d.o[x], d.e[x], lo[x], hi[x]);
+        v[x] = wrap_near(d.c[x] - box.at[x], n[x]) - box.lo[x];
+        in = in && v[x] + lo[x] >= 0 && v[x] + hi[x] < box.ext[x];
+      }
+    }
+    const int stray = few ? 0 : __syncthreads_count(live && !in);
+    if (stray > (brun >= 0 ? DEPOSIT_STRAY : 0)) {
+      if (brun >= 0) flush_box<R, DIM>(run_of(T, brun), box, planes, jm, with_rho == 3);
+      else
+        for (int q = threadIdx.x; q < cap * planes; q += 256) jm[q] = 0.0;
+      const uint64_t m = __ballot(live);
+      const int lead = m ? __ffsll((unsigned long long)m) - 1 : 0;
+      const int lr = __shfl(run, lead, 64);
+      if (lane == 0) wrun[wave] = m ? lr : -1;
+      __syncthreads();
+      brun = uniform(wrun[0] >= 0 ? wrun[0] : (wrun[1] >= 0 ? wrun[1] : (wrun[2] >= 0 ? wrun[2] : wrun[3])));
+      const RunDesc& r = run_of(T, brun);
+      const int n[3] = {r.nx, r.ny, r.nz};
+      const bool here = live && run == brun;
+      box = pick_box<DIM>(here, d.c, lo, hi, n, cap, red);
+      in = here;
+      if (here) {
+#pragma unroll
+        for (int x = 0; x < DIM; ++x) {
+          v[x] = wrap_near(d.c[x] - box.at[x], n[x]) - box.lo[x];
+          in = in && v[x] + lo[x] >= 0 && v[x] + hi[x] < box.ext[x];
+        }
+      }
+      __syncthreads();
+    }
+    if (live) {
+      const SegDesc& s = seg_of(T, seg);
+      const RunDesc& r = run_of(T, run);
+      const PushConst<R> k = push_const<R>(r, s);
+      if (in) {
+        const BoxAcc<R> B{jm, box.ext[0], box.ext[0] * box.ext[1],
+                          box.ext[0] * box.ext[1] * box.ext[2]};
+        if (s.order == 1) deposit<DIM, 1>(B, v, d.o, d.e, d.w, d.vz, k, d.rho);
+        else deposit<DIM, 2>(B, v, d.o, d.e, d.w, d.vz, k, d.rho);
+      } else {
+        const GlobalAcc<R> G = global_acc<R>(r);
+        if (s.order == 1) deposit<DIM, 1>(G, d.c, d.o, d.e, d.w, d.vz, k, d.rho);
+        else deposit<DIM, 2>(G, d.c, d.o, d.e, d.w, d.vz, k, d.rho);
+      }
+    }
   }
+  __syncthreads();
+  if (brun >= 0) flush_box<R, DIM>(run_of(T, brun), box, planes, jm, with_rho == 3);
   // the last workgroup to finish clears the list (every workgroup has read the count by
   // then; no fence: nothing this launch wrote is read before the launch ends)
   __syncthreads();
@@ -675,18 +874,24 @@ int fused_geometry(int dim, int tx, int ty, int tz, int halo) {
 template <typename R, int D, int G>
 static void launch_fused_g(const Tables& T, int nblocks, size_t smem, const Chunk* chunks,
                            const int32_t* nchunks, int with_rho, double* kinetic, int ke_to_diag,
-                           const EscapeList& esc, const int32_t* jshift, PassList pl,
+                           const EscapeList& esc, bool keep, const int32_t* jshift, PassList pl,
                            hipStream_t st) {
-  k_fused<R, D, G><<<nblocks, fused_block<R, D, G>(), smem, st>>>(T, chunks, nchunks, with_rho, kinetic,
-                                               ke_to_diag, esc, jshift, pl);
+  if constexpr (D == 2)
+    if (keep) {
+      k_fused<R, D, G, true><<<nblocks, fused_block<R, D, G>(), smem, st>>>(
+          T, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, (int)smem, jshift, pl);
+      return;
+    }
+  k_fused<R, D, G, false><<<nblocks, fused_block<R, D, G>(), smem, st>>>(
+      T, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, (int)smem, jshift, pl);
 }
 
 template <typename R, int D>
 static void launch_fused_d(int geo, const Tables& T, int nblocks, size_t smem,
                            const Chunk* chunks, const int32_t* nchunks, int with_rho,
-                           double* kinetic, int ke_to_diag, const EscapeList& esc,
+                           double* kinetic, int ke_to_diag, const EscapeList& esc, bool keep,
                            const int32_t* jshift, PassList pl, hipStream_t st) {
-#define LPIC_GEO(g) launch_fused_g<R, D, g>(T, nblocks, smem, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, jshift, pl, st)
+#define LPIC_GEO(g) launch_fused_g<R, D, g>(T, nblocks, smem, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, keep, jshift, pl, st)
   if constexpr (D == 2) {
     switch (geo) {
       case 1: LPIC_GEO(1); return;
@@ -708,39 +913,55 @@ static void launch_fused_d(int geo, const Tables& T, int nblocks, size_t smem,
 #undef LPIC_GEO
 }
 
+template <typename R, int D>
+static void launch_escape(const Tables& T, int with_rho, double* kinetic, int ke_to_diag,
+                          const EscapeList& esc, int skip_at, int blocks, hipStream_t st) {
+  // LDS per workgroup: three workgroups a CU
+  const int smem = 52 * 1024;
+  k_escape<R, D><<<blocks, 256, smem, st>>>(T, with_rho, kinetic, ke_to_diag, esc, skip_at,
+                                            smem / 8 / (3 + charge_planes(with_rho)));
+}
+
 void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size_t smem,
                   const Chunk* chunks, const int32_t* nchunks, int with_rho, double* kinetic,
                   int ke_to_diag, const EscapeList& esc, const int32_t* jshift,
                   hipStream_t st, const Rebin* rb) {
+  const bool keep = dim == 2 && !rb && esc.capacity <= FUSED_KEEP;
   LPIC_PD(prec, dim, (launch_fused_d<R, D>(geo, T, nblocks, smem, chunks, nchunks, with_rho,
-                                           kinetic, ke_to_diag, esc, jshift,
+                                           kinetic, ke_to_diag, esc, keep, jshift,
                                            PassList{nullptr, nullptr}, st)));
+  if (keep) return;
   if (rb) {
     // escapees by present tile, a second pass over them, then whatever that pass could not
-    // place (normally nothing) through global memory
+    // place (normally nothing) and a list below the threshold through global memory
     launch_rebin(T, prec, dim, esc, *rb, st);
     const int k = with_rho == 0 ? 0 : (with_rho == 1 ? 1 : 2);
     LPIC_PD(prec, dim, (launch_fused_d<R, D>(rb->geo[k], T, rb->grid[k], rb->smem[k], rb->chunks,
                                              rb->nchunks, with_rho, kinetic, ke_to_diag,
-                                             rb->esc2, jshift,
+                                             rb->esc2, false, jshift,
                                              PassList{rb->items, esc.rec ? rb->rec : nullptr},
                                              st)));
-    LPIC_PD(prec, dim, (k_escape<R, D><<<ESCAPE_BLOCKS, 256, 0, st>>>(
-                           T, with_rho, kinetic, ke_to_diag, esc, rb->threshold)));
-    LPIC_PD(prec, dim, (k_escape<R, D><<<ESCAPE_BLOCKS, 256, 0, st>>>(
-                           T, with_rho, kinetic, ke_to_diag, rb->esc2, 0x7fffffff)));
+    LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, rb->threshold,
+                                            ESCAPE_BLOCKS, st)));
+    LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, rb->esc2, 0x7fffffff,
+                                            ESCAPE_BLOCKS, st)));
   } else {
-    LPIC_PD(prec, dim, (k_escape<R, D><<<ESCAPE_BLOCKS, 256, 0, st>>>(
-                           T, with_rho, kinetic, ke_to_diag, esc, 0x7fffffff)));
+    const int blocks = (int)std::min<int64_t>(ESCAPE_BLOCKS, (esc.capacity + 255) / 256);
+    LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, 0x7fffffff,
+                                            blocks, st)));
   }
 }
 
 template <typename R, int D, int G>
 static hipError_t set_smem(size_t smem, size_t smem_occ, int* blocks_per_cu) {
-  hipError_t e = hipFuncSetAttribute((const void*)k_fused<R, D, G>,
+  hipError_t e = hipFuncSetAttribute((const void*)k_fused<R, D, G, false>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if constexpr (D == 2)
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)k_fused<R, D, G, true>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_fused<R, D, G>,
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_fused<R, D, G, false>,
                                                       fused_block<R, D, G>(),
                                                       smem_occ);
 }
@@ -787,8 +1008,11 @@ size_t fused_smem_bytes(int prec, int dim, int tx, int ty, int tz, int halo, int
   const int block = geo == 7 || geo == 8
                         ? (prec == 0 ? fused_block<float, 3, 7>() : fused_block<double, 3, 7>())
                         : (prec == 0 ? fused_block<float, 3, 0>() : fused_block<double, 3, 0>());
-  const size_t compact = dim == 3 ? ((size_t)block + 64) * 4 : 0;
-  return plane * 6 * (prec == 0 ? 4 : 8) + plane * jplanes * 8 + compact;
+  const size_t planes = plane * 6 * (prec == 0 ? 4 : 8) + plane * jplanes * 8;
+  // 2D: the list of escaped particles, where the planes leave room for it
+  constexpr size_t room = 160 * 1024 - 512;
+  const size_t list = planes + 8 * FUSED_LIST <= room ? 8 * FUSED_LIST : (planes < room ? room - planes : 0);
+  return planes + (dim == 3 ? ((size_t)block + 64) * 4 : list / 8 * 8);
 }
 
 }  // namespace lpic

@@ -105,10 +105,10 @@ void launch_swap_segments(SegDesc* segs, int nsegs, hipStream_t st);
 // version.
 void launch_build_chunks(const Tables& T, const int32_t* offsets, int nvirt, int chunk,
                          Chunk* out, int32_t* nchunks, hipStream_t st, int32_t* part = nullptr);
-// Particles whose stencils leave the staged region of their home tile: the fused kernel
-// records them here and a second kernel pushes them through global memory (or, re-binned, a
-// second fused pass); the escape kernel's last workgroup
-// clears the list (count[0] entries, count[1] workgroups done) for the next step.
+// Particles whose stencils leave the staged region of their home tile: a list for the escape
+// kernel or, re-binned and from a threshold on, a second fused pass.  The escape kernel's
+// last workgroup clears it (count[0] entries, count[1] workgroups done) for the next step.
+// 2D simulations of up to FUSED_KEEP slots use `items` without the counts (EscapeOut).
 struct EscapeList {
   unsigned long long* items;   // (segment << 32) | particle
   unsigned int* count;         // two counters, zero between steps
@@ -119,7 +119,14 @@ struct EscapeList {
   int32_t* keys = nullptr;     // with records: entry k's (segment, tile) bin by the tile its
                                // particle is in, written with the record
 };
-constexpr int ESCAPE_BLOCKS = 128;
+// Workgroups of the escape kernel (mostly it finds an empty list, and 512 workgroups take
+// 5 us longer than 128 to find that), and entries per workgroup up to which it deals a list
+// out evenly instead of in runs that share a deposit box.
+constexpr int ESCAPE_BLOCKS = 128, ESCAPE_FEW = 64;
+// Slots up to which a 2D simulation without the re-binned path pushes escaped particles in
+// the workgroup that meets them: above, a launch over the list is 1% of a step or less.
+constexpr int64_t FUSED_KEEP = 1 << 20;
+constexpr size_t FUSED_LIST = 512;    // entries of a 2D workgroup's list in LDS
 
 // The re-binned escape path (tiling flag LPIC_ESCAPE_REBIN): when a step's escape list
 // holds at least `threshold` particles, they are grouped by the tile they are in now (bins
@@ -145,8 +152,7 @@ struct Rebin {
 
 // geometry: 0 = runtime strides, else a compiled (tile, halo) shape (fused_geometry()).
 int fused_geometry(int dim, int tx, int ty, int tz, int halo);
-// Launches the fused kernel (persistent grid of nblocks, a multiple of 8) and then the
-// escape kernel on the same stream.
+// Launches the fused kernel (persistent grid of nblocks, a multiple of 8).
 // jshift[run]: the fixed-point shift S of the FP32 current accumulators (launch_fixed_shift).
 // rebin != NULL: the re-binned escape path follows the first pass (see Rebin).
 void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size_t smem,

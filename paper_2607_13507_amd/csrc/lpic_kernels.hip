@@ -824,80 +824,6 @@ __device__ __forceinline__ bool load_path(const SegDesc& s, const RunDesc& r, in
   return true;
 }
 
-// Accumulator over a box of nodes in LDS (FP64 in both precisions): planes Jx Jy Jz, then
-// rho0 rho1; coordinates relative to the box's first node.
-template <typename R>
-struct BoxAcc {
-  static constexpr bool kPaired = false;
-  static constexpr bool kLinear = true;
-  double* j;
-  int sy, sz, plane;
-  __device__ __forceinline__ int xo(int x) const { return x; }
-  __device__ __forceinline__ int yo(int y) const { return y * sy; }
-  __device__ __forceinline__ int zo(int z) const { return z * sz; }
-  __device__ __forceinline__ R fold() const { return R(1); }
-  __device__ __forceinline__ void add_core(int comp, int off, R v) const {
-    atomic_add_lds(j + (comp - F_JX) * plane + off, (double)v);
-  }
-  __device__ __forceinline__ void add(int comp, int off, R v) const {
-    if (v != R(0)) add_core(comp, off, v);
-  }
-};
-
-// A box of nodes: `at` an anchor cell, the box spans [at + lo, at + lo + ext) per axis.
-struct NodeBox {
-  int at[3], lo[3], ext[3];
-};
-
-// v in the range [-n/2, n - n/2) around 0 modulo n (v within one n of it).
-__device__ __forceinline__ int wrap_near(int v, int n) {
-  const int h = n >> 1;
-  return v >= n - h ? v - n : (v < -h ? v + n : v);
-}
-
-// The nodes a path touches on one axis, relative to its start cell (see deposit_fits).
-template <int ORDER, typename R>
-__device__ __forceinline__ void path_nodes(R po, R pe, int& lo, int& hi) {
-  if constexpr (ORDER == 1) {
-    const int c1 = (int)floor_clamped<R>(pe, R(-1), R(1));
-    lo = c1 < 0 ? c1 : 0;
-    hi = lo + 1 + (c1 != 0);
-  } else {
-    const int c0 = po >= R(0.5);
-    const int c1 = (int)floor_clamped<R>(pe + R(0.5), R(-1), R(2));
-    lo = (c0 < c1 ? c0 : c1) - 1;
-    hi = lo + 2 + (c0 != c1);
-  }
-}
-
-// Adds the box's sums to the global arrays (one atomic per non-zero entry) and clears them.
-template <typename R, int DIM>
-__device__ __forceinline__ void flush_box(const RunDesc& r, const NodeBox& b, int planes,
-                                          double* jm) {
-  gptr<R> F[5];
-#pragma unroll
-  for (int c = 0; c < 5; ++c) F[c] = gp((R*)r.f[F_JX + c]);
-  const int n[3] = {r.nx, r.ny, r.nz};
-  const int plane = b.ext[0] * b.ext[1] * b.ext[2];
-  for (int i = threadIdx.x; i < plane; i += 256) {
-    int x[3];
-    x[0] = i % b.ext[0];
-    const int rest = i / b.ext[0];
-    x[1] = DIM == 3 ? rest % b.ext[1] : rest;
-    x[2] = DIM == 3 ? rest / b.ext[1] : 0;
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) x[d] = wrapm(b.at[d] + b.lo[d] + x[d], n[d]);
-    const int64_t g = ((int64_t)x[2] * n[1] + x[1]) * n[0] + x[0];
-    for (int c = 0; c < planes; ++c) {
-      const double v = jm[c * plane + i];
-      if (v != 0.0) {
-        atomic_add_global(F[c] + g, R(v));
-        jm[c * plane + i] = 0.0;
-      }
-    }
-  }
-}
-
 // Deposit of the split path, 256 particles per pass and `per` passes per workgroup.  One
 // global atomic per window entry (39 in 2D, 150 in 3D, quadratic) runs at about 60 G/s on
 // the chip, whatever the particles' order; particles that lie near each other (as loaded
@@ -911,8 +837,6 @@ __device__ __forceinline__ void flush_box(const RunDesc& r, const NodeBox& b, in
 // A pass whose box does not fit takes one of up to 2.5 standard deviations around the mean
 // per axis, cut to `cap` nodes; the windows outside the box (of that pass, and up to
 // DEPOSIT_STRAY of a later one) go to memory directly.
-constexpr int DEPOSIT_STRAY = 16;
-
 template <typename R, int DIM, int ORDER>
 __device__ __forceinline__ void deposit_passes(const SegDesc& s, const RunDesc& r,
                                                const void* old, int planes, int per, int cap,
@@ -950,93 +874,7 @@ __device__ __forceinline__ void deposit_passes(const SegDesc& s, const RunDesc& 
         flush_box<R, DIM>(r, box, planes, jm);
         __syncthreads();
       }
-      // the new box: anchor at a live particle's cell, bounds over the windows
-      const uint64_t m = __ballot(live);
-      const int first = m ? __ffsll((unsigned long long)m) - 1 : 0;
-      int a[3];
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) a[d] = __shfl(path.c[d], first, 64);
-      if (lane == 0) {
-        red[wave][0] = m != 0;
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) red[wave][1 + d] = a[d];
-      }
-      __syncthreads();
-      const int w = red[0][0] ? 0 : (red[1][0] ? 1 : (red[2][0] ? 2 : 3));
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) box.at[d] = uniform(red[w][1 + d]);
-      __syncthreads();
-      constexpr int FAR = 1 << 28;
-      int mn[3], mx[3];
-      float sum[3], sq[3];
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        v[d] = live ? wrap_near(path.c[d] - box.at[d], n[d]) : 0;
-        mn[d] = -wave_max(live ? -(v[d] + lo[d]) : -FAR);
-        mx[d] = wave_max(live ? v[d] + hi[d] : -FAR);
-        sum[d] = wave_sum((float)v[d]);
-        sq[d] = wave_sum((float)v[d] * (float)v[d]);
-      }
-      if (lane == 0) {
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          red[wave][d] = mn[d];
-          red[wave][3 + d] = mx[d];
-          red[wave][6 + d] = __float_as_int(sum[d]);
-          red[wave][9 + d] = __float_as_int(sq[d]);
-        }
-        red[wave][12] = __popcll(m);
-      }
-      __syncthreads();
-      const float cnt = (float)uniform(red[0][12] + red[1][12] + red[2][12] + red[3][12]);
-      int64_t nodes = 1, wider = 1;
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        mn[d] = uniform(min(min(red[0][d], red[1][d]), min(red[2][d], red[3][d])));
-        mx[d] = uniform(max(max(red[0][3 + d], red[1][3 + d]), max(red[2][3 + d], red[3][3 + d])));
-        box.lo[d] = mn[d];
-        box.ext[d] = mx[d] - mn[d] + 1;
-        nodes *= box.ext[d];
-        wider *= box.ext[d] + 2;
-      }
-      if (wider <= cap) {          // room for the next pass's particles around them
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) { box.lo[d] -= 1; box.ext[d] += 2; }
-      } else if (nodes > cap) {    // too many nodes: without the far particles of each axis
-        float prod = 1.0f;
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          const float sd = __int_as_float(uniform(__float_as_int(
-                    __int_as_float(red[0][6 + d]) + __int_as_float(red[1][6 + d]) +
-                    __int_as_float(red[2][6 + d]) + __int_as_float(red[3][6 + d])))) / cnt;
-          const float qd = __int_as_float(uniform(__float_as_int(
-                    __int_as_float(red[0][9 + d]) + __int_as_float(red[1][9 + d]) +
-                    __int_as_float(red[2][9 + d]) + __int_as_float(red[3][9 + d])))) / cnt;
-          const float want = 5.0f * sqrtf(fmaxf(qd - sd * sd, 0.0f)) + 6.0f;
-          if (want < (float)box.ext[d]) {
-            box.ext[d] = (int)want;
-            box.lo[d] = (int)sd - box.ext[d] / 2;
-          }
-          prod *= (float)box.ext[d];
-        }
-        if (prod > (float)cap) {
-          const float f = DIM == 2 ? sqrtf((float)cap / prod) : cbrtf((float)cap / prod);
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) {
-            const int e = max(8, (int)((float)box.ext[d] * f));
-            if (e < box.ext[d]) {
-              box.lo[d] += (box.ext[d] - e) / 2;
-              box.ext[d] = e;
-            }
-          }
-          // an axis kept at 8 nodes leaves the others too long by its share
-          while ((int64_t)box.ext[0] * box.ext[1] * box.ext[2] > cap) {
-            int& x = box.ext[0] >= box.ext[1] && box.ext[0] >= box.ext[2] ? box.ext[0]
-                   : (box.ext[1] >= box.ext[2] ? box.ext[1] : box.ext[2]);
-            x = x > 16 ? x - x / 8 : x - 1;
-          }
-        }
-      }
+      box = pick_box<DIM>(live, path.c, lo, hi, n, cap, red);
       if (!have)                   // (a flush leaves zeros; the first box clears all it can use)
         for (int i = threadIdx.x; i < cap * planes; i += 256) jm[i] = 0.0;
       have = true;
@@ -1044,7 +882,7 @@ __device__ __forceinline__ void deposit_passes(const SegDesc& s, const RunDesc& 
       if (live) {
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
-          v[d] -= box.lo[d];
+          v[d] = wrap_near(path.c[d] - box.at[d], n[d]) - box.lo[d];
           in = in && v[d] + lo[d] >= 0 && v[d] + hi[d] < box.ext[d];
         }
       }

@@ -1,0 +1,86 @@
+"""Particles that have left their tile's staged region, in large numbers: the workgroups'
+lists in LDS (and what overflows them), the escape kernel's short lists and its deposit boxes,
+and the workgroups that push their own (2D boxes of up to 2^20 slots), against the split path
+on a copy of the same slots (which uses neither tiles nor lists).
+
+Tolerances: the arithmetic per particle is the same in both paths, so FP64 agrees to the order
+of the sums (1e-11 of each component's largest value) and particles to 1e-12; FP32 sums are
+rounded at different places (2e-5 of the largest value, particles 2e-6)."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import banner
+from paper_2607_13507_amd import lpic as L
+from paper_2607_13507_amd import workloads as W
+from paper_2607_13507_amd.simulation import DeviceFields, DeviceSpecies, grid_struct
+
+pytestmark = pytest.mark.gpu
+CURRENT = ("jx", "jy", "jz")
+
+CASES = [  # ndim, nx, ny, ppc, order, share of the particles moved away
+    (2, 512, 256, 9, 2, 0.004), (2, 512, 256, 9, 2, 0.4), (2, 512, 256, 9, 1, 1.0),
+    (2, 100, 60, 9, 2, 0.5), (3, 40, 0, 4, 2, 0.01), (3, 40, 0, 4, 1, 0.6),
+]
+
+
+@pytest.mark.parametrize("prec", [L.F64_ABS, L.F32_CELLOFS], ids=["f64", "f32"])
+@pytest.mark.parametrize("ndim,nx,ny,ppc,order,share", CASES)
+def test_escaped_particles(prec, ndim, nx, ny, ppc, order, share):
+    banner(f"escapes {ndim}D {nx}x{ny} ppc={ppc} order={order} share={share} prec={prec}")
+    wl = (W.thermal_2d(nx=nx, ny=ny, dx=0.1, ppc=ppc, T=0.3, order=order, seed=31) if ndim == 2
+          else W.thermal_3d(n=nx, dx=0.1, ppc=ppc, T=0.3, order=order, seed=32))
+    wl.fields = W.random_fields(wl.ncell, 33, 0.5)
+    grid = grid_struct(wl)
+    F, G = DeviceFields(wl, prec), DeviceFields(wl, prec)
+    a = DeviceSpecies.from_init(grid, wl.species[0], prec)
+    n, st = a.n, a.struct()
+    alt = a.like()
+    t = L.Tiling(16, 16, 1, 5, 1024, 0) if ndim == 2 else L.Tiling(8, 4, 4, 3, 1024, 0)
+    off = torch.empty(L.lpic_num_tiles(grid, t) + 2, dtype=torch.int32, device="cuda")
+    size = L.lpic_sort_ws_bytes(grid, t, n)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    L.lpic_sort_tiles(grid, st, alt.struct(), t, off.data_ptr(), ws.data_ptr(), size, prec)
+    torch.cuda.synchronize()
+    a = alt                                    # the sorted arrays
+    # a share of the slots, contiguous ranges among them, moves half a box away
+    pos = a.positions(grid)
+    rng = np.random.default_rng(3)
+    move = rng.random(n) < share
+    move[n // 3:n // 3 + int(0.2 * share * n)] = True
+    for d in range(ndim):
+        box = (grid.nx * grid.dx, grid.ny * grid.dy, grid.nz * grid.dz)[d]
+        p = pos[d] + 0.5 * box * move
+        pos[d] = np.where(p >= box, p - box, p)
+    a.load_positions(grid, pos[0], pos[1], pos[2] if ndim == 3 else None)
+    b = a.like()
+    for k, v in a.a.items():
+        b.a[k].copy_(v)
+    size = L.lpic_fused_ws_bytes(grid, t, n)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    ke = torch.zeros(1, dtype=torch.float64, device="cuda")
+    L.lpic_push_deposit_fused(grid, F.struct(), a.struct(), t, off.data_ptr(), ws.data_ptr(), size,
+                              1, ke.data_ptr(), prec)
+    size = L.lpic_old_state_bytes(ndim, n, prec)
+    old = torch.empty(size, dtype=torch.uint8, device="cuda")
+    L.lpic_gather_push(grid, G.struct(), b.struct(), old.data_ptr(), size, prec)
+    L.lpic_deposit_esirkepov(grid, G.struct(), b.struct(), old.data_ptr(), size, 1, prec)
+    torch.cuda.synchronize()
+    tol, ptol = (1e-11, 1e-12) if prec == L.F64_ABS else (2e-5, 2e-6)
+    f, g = F.numpy(), G.numpy()
+    for k in CURRENT + ("rho0", "rho1"):
+        scale = np.abs(g[k]).max()
+        assert np.abs(f[k] - g[k]).max() <= tol * scale, k
+    pa, pb = a.positions(grid), b.positions(grid)
+    for d in range(ndim):
+        box = (grid.nx * grid.dx, grid.ny * grid.dy, grid.nz * grid.dz)[d]
+        e = pa[d] - pb[d]
+        assert np.abs(e - box * np.round(e / box)).max() <= ptol * box, d
+    u2 = 0.0
+    for k in ("ux", "uy", "uz"):
+        ua, ub = a.numpy(k).astype(np.float64), b.numpy(k).astype(np.float64)
+        assert np.abs(ua - ub).max() <= ptol * max(1.0, np.abs(ub).max()), k
+        u2 = u2 + ub * ub
+    w = b.numpy("w").astype(np.float64)
+    want = (w * u2 / (1.0 + np.sqrt(1.0 + u2))).sum()
+    assert abs(ke.item() - want) <= (1e-11 if prec == L.F64_ABS else 1e-6) * want
