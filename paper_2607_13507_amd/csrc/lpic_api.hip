@@ -300,7 +300,7 @@ lpic_status lpic_yee_update_EB(const lpic_grid* grid, const lpic_fields* fields,
   Tables T = single_tables(r, nullptr);
   const int64_t nb = (ncells(grid) + 255) / 256;
   launch_yee(T, prec, grid->ndim, (int)nb, which, frac, (flags & LPIC_YEE_ZERO_J) ? 1 : 0, 1,
-             stream);
+             stream, yee_rows(r, prec));
   return last_launch("yee");
 }
 
@@ -874,6 +874,7 @@ struct lpic_sim {
   // fused 2D field update between steps (launch_yee_mid); mid_tx == 0: not in use
   int mid_tx = 0, mid_ty = 0, mid_ntiles = 0;
   bool mid_divides = false;                  // the tile divides every box
+  bool rows = false;                         // every box satisfies yee_rows
   int32_t* mid_pfx_d = nullptr;              // nruns + 1 prefix of field tiles
   void* set2 = nullptr;                      // E, B and J of the second field set
   size_t set2_bytes = 0;
@@ -1001,6 +1002,8 @@ lpic_status configure(lpic_sim* s) {
     s->runs_h.push_back(d);
     run_blk.push_back(run_blk.back() + (int32_t)((ncells(&s->grids[r]) + 255) / 256));
   }
+  s->rows = true;   // (the second field set's arrays are aligned to 256 bytes)
+  for (const RunDesc& d : s->runs_h) s->rows = s->rows && yee_rows(d, s->prec);
   // segments (current buffers first)
   s->segs_h.clear();
   std::vector<int32_t> blk256(1, 0), blks(1, 0);
@@ -1280,6 +1283,7 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
   const Tables Tc = sim_tables(s, nullptr, set);
   const Tables Ts = sim_tables(s, s->seg_blk_sort_d, set);
   const bool mid = s->mid_tx > 0;
+  const bool rows = s->rows;
   int64_t* clock = s->laser_bpr > 0 ? s->step_dev : nullptr;
   if (diag) {
     launch_diag_clear(Tc, s->nruns, st);
@@ -1298,9 +1302,9 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
     const int zero = rho == 1 ? 1 : (rho == 2 ? 3 : (rho == 3 ? 4 : 2));
     const RunDesc* out = move ? Tc.runs : nullptr;
     launch_yee(T0, s->prec, s->ndim, s->nblk_cells, 0, first_full ? 1.0 : 0.5, zero,
-               first_full ? 2 : 1, st, out, clock);
+               first_full ? 2 : 1, st, rows, out, clock);
     CHK(last_launch("yee E"));
-    launch_yee(T0, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st, out);
+    launch_yee(T0, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st, rows, out);
     CHK(last_launch("yee B"));
   }
   if (eager_hooks) CHK(run_hooks(s, LPIC_STAGE_MAXWELL_1));
@@ -1412,10 +1416,10 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
     CHK(last_launch("yee fused"));
   } else {
     // field half update t + dt/2 -> t + dt (B first)
-    launch_yee(Tc, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st);
+    launch_yee(Tc, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st, rows);
     CHK(last_launch("yee B"));
     if (!skip_last) {
-      launch_yee(Tc, s->prec, s->ndim, s->nblk_cells, 0, 0.5, 0, 1, st);
+      launch_yee(Tc, s->prec, s->ndim, s->nblk_cells, 0, 0.5, 0, 1, st, rows);
       CHK(last_launch("yee E"));
     }
   }

@@ -65,9 +65,12 @@ __host__ __device__ inline int mid_shift(bool mur, int nx, int tx) {
 // update stands for two equal half updates (open x ends apply their condition twice).
 // out != NULL: the runs of the other field set, which the update writes (an E update, then a
 // B update, move a simulation there; clock: its two antenna clock words or NULL).
+// rows: every run satisfies yee_rows() (four cells per thread).
 void launch_yee(const Tables& T, int prec, int dim, int nblocks, int which, double frac,
-                int zero_j, int halves, hipStream_t st, const RunDesc* out = nullptr,
-                int64_t* clock = nullptr);
+                int zero_j, int halves, hipStream_t st, bool rows,
+                const RunDesc* out = nullptr, int64_t* clock = nullptr);
+// Rows of whole groups of four cells, arrays aligned to such a group.
+bool yee_rows(const RunDesc& r, int prec);
 // The three field updates between two particle pushes of 2D steps, fused: B by dt/2, E by
 // dt (two merged halves, with the J in place), B by dt/2 -- the last half update of one
 // step and the first two of the next, from the set of T into the other one, whose J is
