@@ -740,7 +740,7 @@ lpic_status lpic_push_deposit_fused(const lpic_grid* grid, const lpic_fields* fi
   int bpc = 1;
   HIPCHK(prepare_fused(prec, grid->ndim, geo, smem, smem, &bpc));
   launch_fused(T, prec, grid->ndim, geo, fused_grid(maxch, bpc), smem, chunks, nchunks, with_rho,
-               kinetic, 0, esc, jshift, stream);
+               kinetic, 0, esc, jshift, stream, nullptr, true);
   return last_launch("fused");
 }
 

@@ -503,7 +503,8 @@ __device__ __forceinline__ double process_chunk(const RunDesc& r, const SegDesc&
                                                 const Chunk& ch, const Region& g,
                                                 const LA& L, int with_rho,
                                                 bool want_ke, const EscapeOut& out,
-                                                const PassList& pl, int32_t* cbuf) {
+                                                const PassList& pl, int32_t* cbuf,
+                                                bool by_four) {
   // 3D: compacted rounds, except for the second pass of the re-binned path on the two-per-CU
   // geometry (DIRECT), whose particles lie inside their present tile (nearly all on chip):
   // there the records are loaded directly, one memory latency and no barriers per round
@@ -518,13 +519,17 @@ __device__ __forceinline__ double process_chunk(const RunDesc& r, const SegDesc&
   double ke = 0.0;
   constexpr int BATCH = batch_of<R, DIM>();
   const int32_t span = (int32_t)blockDim.x * BATCH;
+  // the particle of a thread in a batch of blockDim: 2D by_four, neighbours go to the four
+  // waves of the workgroup (cell_order)
+  const int32_t at = DIM == 2 && by_four ? (int32_t)(4 * (threadIdx.x & 63) + (threadIdx.x >> 6))
+                                         : (int32_t)threadIdx.x;
   for (int32_t base = ch.beg; base < ch.end; base += span) {
     PState<R> ps[BATCH];
     int32_t pi[BATCH];
     bool ok[BATCH];
 #pragma unroll
     for (int b = 0; b < BATCH; ++b) {
-      const int32_t lp = base + b * (int32_t)blockDim.x + (int32_t)threadIdx.x;
+      const int32_t lp = base + b * (int32_t)blockDim.x + at;
       ok[b] = lp < ch.end;
       pi[b] = lp;
       if (pl.list && ok[b]) pi[b] = (int32_t)(gp(pl.list)[lp] & 0xffffffffull);
@@ -612,6 +617,28 @@ __device__ __forceinline__ T block_sum(T v, T* red) {
   return t;
 }
 
+// Whether particles that share a cell lie side by side in the stream from slot p on: at
+// least CELL_PAIRS pairs of its first 64 that are up to 7 apart (two a cell in cell order give
+// 32, eight 224 or, after a cell's worth of drift, about 70; a mixed order of 256 cells 2).
+// Adds of one wave to one address serialise, so such a stream is dealt to the workgroup's
+// waves in turn (by_four).  1000 x 750 cells with charge, a stateless step, in slot order and
+// dealt out: 8 a cell FP64 530 and 442 us, FP32 356 and 288; 4 a cell FP32 189 and 176; 1 or
+// 2 a cell within 1%.  A mixed stream would only lose (four times the lines per load: 3% in
+// FP64, 9% in FP32), so lpic_step, whose first sort spreads every tile, does not ask.
+constexpr int CELL_PAIRS = 16;
+
+template <typename R>
+__device__ __forceinline__ bool cell_order(const PartPtrs<R>& q, int32_t p, int32_t end) {
+  const int lane = __lane_id();
+  int c[3] = {-1, -1, 0};
+  const bool ok = p + lane < end && load_cell<R, 2>(q, p + lane, c);
+  const int key = ok ? c[1] * q.nx + c[0] : -1 - lane;
+  int pairs = 0;
+#pragma unroll
+  for (int d = 1; d < 8; ++d) pairs += __popcll(__ballot(key == __shfl_up(key, d, 64) && lane >= d));
+  return pairs >= CELL_PAIRS;
+}
+
 // A descriptor copied into wavefront-uniform registers word by word.  Every lane holds the
 // same descriptor, but loaded through a generic reference (the device table, or the copy in
 // the kernel arguments) its words land in vector registers; with the particle loop's
@@ -638,7 +665,7 @@ template <typename R, int DIM, int G, bool KEEP>
 __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_waves_per_eu(fused_waves<R, DIM, G>()))) void k_fused(Tables T, const Chunk* chunks,
                                                const int32_t* nchunks, int with_rho,
                                                double* kinetic, int ke_to_diag,
-                                               EscapeList esc, int list_end,
+                                               EscapeList esc, int list_end, int probe,
                                                const int32_t* jshift, PassList pl) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double red[fused_block<R, DIM, G>() / 64];
@@ -681,6 +708,13 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
   // (2D: the LDS list takes the launch's LDS after the current planes, up to list_end)
   EscapeOut out{esc, &kept, (unsigned long long*)cbuf, (list_end - (int)((unsigned char*)cbuf - smem_raw)) / 8, 0};
   if (threadIdx.x == 0) kept = 0;   // (staging's barrier comes before the first append)
+  bool by_four = false;
+  if constexpr (DIM == 2) {
+    if (probe) {
+      const int32_t beg = uniform(chunks[lo].beg), end = uniform(chunks[lo].end);
+      by_four = cell_order<R>(part_ptrs<R>(s0, run_of(T, s0.run)), beg, end);
+    }
+  }
   int cur_run = -1, cur_tile = -1, cur_seg = -1;
   Region g;
   double ke = 0.0;
@@ -724,8 +758,8 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
     const RunDesc r = run_of(T, s.run);
     const bool want_ke = kinetic || ke_to_diag;
     ke += s.order == 1
-              ? process_chunk<R, DIM, 1, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf)
-              : process_chunk<R, DIM, 2, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf);
+              ? process_chunk<R, DIM, 1, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf, by_four)
+              : process_chunk<R, DIM, 2, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf, by_four);
   }
   const RunDesc& rl = run_of(T, cur_run);
   ke += drain_escapes<R, DIM, KEEP>(T, cur_seg, out, with_rho);
@@ -874,24 +908,24 @@ int fused_geometry(int dim, int tx, int ty, int tz, int halo) {
 template <typename R, int D, int G>
 static void launch_fused_g(const Tables& T, int nblocks, size_t smem, const Chunk* chunks,
                            const int32_t* nchunks, int with_rho, double* kinetic, int ke_to_diag,
-                           const EscapeList& esc, bool keep, const int32_t* jshift, PassList pl,
-                           hipStream_t st) {
+                           const EscapeList& esc, bool keep, int probe, const int32_t* jshift,
+                           PassList pl, hipStream_t st) {
   if constexpr (D == 2)
     if (keep) {
       k_fused<R, D, G, true><<<nblocks, fused_block<R, D, G>(), smem, st>>>(
-          T, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, (int)smem, jshift, pl);
+          T, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, (int)smem, probe, jshift, pl);
       return;
     }
   k_fused<R, D, G, false><<<nblocks, fused_block<R, D, G>(), smem, st>>>(
-      T, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, (int)smem, jshift, pl);
+      T, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, (int)smem, probe, jshift, pl);
 }
 
 template <typename R, int D>
 static void launch_fused_d(int geo, const Tables& T, int nblocks, size_t smem,
                            const Chunk* chunks, const int32_t* nchunks, int with_rho,
-                           double* kinetic, int ke_to_diag, const EscapeList& esc, bool keep,
+                           double* kinetic, int ke_to_diag, const EscapeList& esc, bool keep, int probe,
                            const int32_t* jshift, PassList pl, hipStream_t st) {
-#define LPIC_GEO(g) launch_fused_g<R, D, g>(T, nblocks, smem, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, keep, jshift, pl, st)
+#define LPIC_GEO(g) launch_fused_g<R, D, g>(T, nblocks, smem, chunks, nchunks, with_rho, kinetic, ke_to_diag, esc, keep, probe, jshift, pl, st)
   if constexpr (D == 2) {
     switch (geo) {
       case 1: LPIC_GEO(1); return;
@@ -925,10 +959,10 @@ static void launch_escape(const Tables& T, int with_rho, double* kinetic, int ke
 void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size_t smem,
                   const Chunk* chunks, const int32_t* nchunks, int with_rho, double* kinetic,
                   int ke_to_diag, const EscapeList& esc, const int32_t* jshift,
-                  hipStream_t st, const Rebin* rb) {
+                  hipStream_t st, const Rebin* rb, bool probe) {
   const bool keep = dim == 2 && !rb && esc.capacity <= FUSED_KEEP;
   LPIC_PD(prec, dim, (launch_fused_d<R, D>(geo, T, nblocks, smem, chunks, nchunks, with_rho,
-                                           kinetic, ke_to_diag, esc, keep, jshift,
+                                           kinetic, ke_to_diag, esc, keep, probe ? 1 : 0, jshift,
                                            PassList{nullptr, nullptr}, st)));
   if (keep) return;
   if (rb) {
@@ -938,7 +972,7 @@ void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size
     const int k = with_rho == 0 ? 0 : (with_rho == 1 ? 1 : 2);
     LPIC_PD(prec, dim, (launch_fused_d<R, D>(rb->geo[k], T, rb->grid[k], rb->smem[k], rb->chunks,
                                              rb->nchunks, with_rho, kinetic, ke_to_diag,
-                                             rb->esc2, false, jshift,
+                                             rb->esc2, false, 0, jshift,
                                              PassList{rb->items, esc.rec ? rb->rec : nullptr},
                                              st)));
     LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, rb->threshold,

@@ -157,11 +157,12 @@ struct Rebin {
 int fused_geometry(int dim, int tx, int ty, int tz, int halo);
 // Launches the fused kernel (persistent grid of nblocks, a multiple of 8).
 // jshift[run]: the fixed-point shift S of the FP32 current accumulators (launch_fixed_shift).
-// rebin != NULL: the re-binned escape path follows the first pass (see Rebin).
+// rebin != NULL: the re-binned escape path follows the first pass (see Rebin).  probe: the
+// stream may lie cell by cell (2D: the kernel looks and deals it out, see cell_order).
 void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size_t smem,
                   const Chunk* chunks, const int32_t* nchunks, int with_rho, double* kinetic,
                   int ke_to_diag, const EscapeList& esc, const int32_t* jshift,
-                  hipStream_t st, const Rebin* rebin = nullptr);
+                  hipStream_t st, const Rebin* rebin = nullptr, bool probe = false);
 // Escape-list entries to (segment, present tile) bins and their grouped list (the first
 // three kernels of the re-binned path), then the chunk list over those bins.
 void launch_rebin(const Tables& T, int prec, int dim, const EscapeList& esc, const Rebin& rb,

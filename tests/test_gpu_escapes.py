@@ -84,3 +84,41 @@ def test_escaped_particles(prec, ndim, nx, ny, ppc, order, share):
     w = b.numpy("w").astype(np.float64)
     want = (w * u2 / (1.0 + np.sqrt(1.0 + u2))).sum()
     assert abs(ke.item() - want) <= (1e-11 if prec == L.F64_ABS else 1e-6) * want
+
+
+@pytest.mark.parametrize("prec", [L.F64_ABS, L.F32_CELLOFS], ids=["f64", "f32"])
+@pytest.mark.parametrize("nx,ny,ppc,order,chunk", [(48, 32, 8, 2, 1024), (40, 20, 3, 1, 100),
+                                                   (16, 16, 40, 2, 257), (20, 12, 1, 2, 64)])
+def test_stream_in_cell_order(prec, nx, ny, ppc, order, chunk):
+    """The stateless fused call on tiles whose particles lie cell by cell (dealt to the waves in
+    turn), in full and ragged batches, against the split path on the same slots."""
+    banner(f"cell order {nx}x{ny} ppc={ppc} chunk={chunk} prec={prec}")
+    wl = W.thermal_2d(nx=nx, ny=ny, dx=0.1, ppc=ppc, T=0.1, order=order, seed=41)
+    wl.fields = W.random_fields(wl.ncell, 42, 0.5)
+    s = wl.species[0]
+    tile = (np.floor(s.y / 0.1).astype(int) // 16) * -(-nx // 16) + np.floor(s.x / 0.1).astype(int) // 16
+    by = np.argsort(tile, kind="stable")
+    for k in ("x", "y", "ux", "uy", "uz", "w"):
+        setattr(s, k, np.ascontiguousarray(getattr(s, k)[by]))
+    grid = grid_struct(wl)
+    F, G = DeviceFields(wl, prec), DeviceFields(wl, prec)
+    a, b = (DeviceSpecies.from_init(grid, s, prec) for _ in range(2))
+    t = L.Tiling(16, 16, 1, 5, chunk, 0)
+    nt = L.lpic_num_tiles(grid, t)
+    off = np.concatenate([[0], np.cumsum(np.bincount(tile, minlength=nt)), [a.n]]).astype(np.int32)
+    off = torch.from_numpy(off).cuda()
+    size = L.lpic_fused_ws_bytes(grid, t, a.n)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    L.lpic_push_deposit_fused(grid, F.struct(), a.struct(), t, off.data_ptr(), ws.data_ptr(), size,
+                              1, None, prec)
+    size = L.lpic_old_state_bytes(2, a.n, prec)
+    old = torch.empty(size, dtype=torch.uint8, device="cuda")
+    L.lpic_gather_push(grid, G.struct(), b.struct(), old.data_ptr(), size, prec)
+    L.lpic_deposit_esirkepov(grid, G.struct(), b.struct(), old.data_ptr(), size, 1, prec)
+    torch.cuda.synchronize()
+    tol, ptol = (1e-11, 1e-12) if prec == L.F64_ABS else (2e-5, 2e-6)
+    f, g = F.numpy(), G.numpy()
+    for k in CURRENT + ("rho0", "rho1"):
+        assert np.abs(f[k] - g[k]).max() <= tol * np.abs(g[k]).max(), k
+    for k in ("ux", "uy", "uz"):
+        assert np.abs(a.numpy(k) - b.numpy(k)).max() <= ptol, k
