@@ -250,7 +250,7 @@ struct EscapeOut {
   EscapeList list;
   int32_t* count;              // LDS: entries kept, or in the LDS list
   unsigned long long* lds;     // the LDS list (2D without KEEP): segment << 32 | slot
-  int cap;
+  int cap;                     // entries the LDS list holds (3D: waiting slots of the rounds)
   int64_t base;                // KEEP
 };
 
@@ -411,10 +411,39 @@ __device__ __forceinline__ bool push_on_chip(const RunDesc& r, const Region& g, 
 
 // 3D rounds with compaction (one particle per thread per round): each thread first reads
 // only its particle's cell and classifies it (on chip / escaped / none); the on-chip
-// particles of the workgroup are then packed into the first threads (their slots pass
-// through LDS) and pushed there, so no wave carries idle lanes for escaped particles; the
-// escaped ones are appended to the escape list with one global reservation per round.
-// cbuf: blockDim + 64 words of LDS.
+// particles of the workgroup are then packed into the first threads (their places in the
+// round pass through LDS) and pushed there, so no wave carries idle lanes for escaped
+// particles.  One barrier per round: the list of a round and its counts (three, taken in
+// turn) are not written again before every wave has passed the next barrier.  The cells of
+// the next round are loaded while this one is pushed.  Escaped particles wait in LDS and go
+// to the escape list by the hundred: a reservation per round kept every round waiting for a
+// global atomic and for the loads of a few records.  (Three barriers and a reservation per
+// round, then one: 256^3 FP32, 134M particles, 368.3 and 355.6 ms per 20 steps.)
+constexpr int ROUND_ESC = 256;
+
+// LDS of the rounds, in words, for a workgroup of bd threads and `wait` waiting particles:
+// ROUND_ESC in the fixed geometries (all fit), with runtime strides what the planes leave, at
+// least 56.
+constexpr int ROUND_ESC_MIN = 56;
+__host__ __device__ constexpr int round_words(int bd, int wait) { return bd + wait + 8; }
+
+// The waiting escaped particles to the escape list (every thread calls it).
+template <typename R, int DIM>
+__device__ __forceinline__ void flush_waiting(const EscapeList& esc, const int32_t* wait, int m,
+                                              int32_t* gbase, int seg, const PartPtrs<R>& q,
+                                              const RunDesc& r, const SegDesc& s) {
+  if (threadIdx.x == 0) *gbase = (int32_t)atomicAdd(esc.count, (unsigned int)m);
+  __syncthreads();
+  const int64_t base = (int64_t)(uint32_t)*gbase;
+  for (int e = (int)threadIdx.x; e < m; e += (int)blockDim.x)
+    if (base + e < esc.capacity) {
+      const int32_t es = wait[e];
+      esc.items[base + e] = ((unsigned long long)seg << 32) | (unsigned long long)(uint32_t)es;
+      if (esc.rec) escape_record<R, DIM>(esc, base + e, r, s, q, es);
+    }
+  __syncthreads();                     // the list and gbase may be written again
+}
+
 template <typename R, int DIM, int ORDER, class LA>
 __device__ __forceinline__ double process_chunk_compact(
     const RunDesc& r, const SegDesc& s, int seg, const Chunk& ch, const Region& g, const LA& L,
@@ -424,65 +453,78 @@ __device__ __forceinline__ double process_chunk_compact(
   const PushConst<R> k = push_const<R>(r, s);
   const PartPtrs<R> q = part_ptrs<R>(s, r);
   const int bd = (int)blockDim.x, tid = (int)threadIdx.x;
-  const int lane = __lane_id(), wv = tid >> 6, nw = bd >> 6;
-  // one list of bd entries: the on-chip particles (slots; list indexes when their records
-  // are read) packed from the front, the slots of the escaped ones from the back
-  int32_t* cin = cbuf;
-  int32_t* wsum = cbuf + bd;           // per wave: on-chip and escaped counts -> bases;
-                                       // [2 nw], [2 nw + 1]: totals; [2 nw + 2]: list base
+  const int lane = __lane_id();
+  const uint64_t below = (1ull << lane) - 1ull;
+  uint16_t* list = (uint16_t*)cbuf;    // two lists of bd places
+  const int room = out.cap;            // escaped slots that may wait
+  int32_t* cnt = cbuf + bd;            // [0..2] on chip, [3..5] escaped, by round modulo 3
+  int32_t* gbase = cnt + 6;
+  int32_t* wait = cnt + 8;
+  if (tid < 6) cnt[tid] = 0;
+  __syncthreads();
   double ke = 0.0;
+  int pend = 0;                        // escaped particles waiting (uniform)
+  int turn = 0, side = 0;
+  // the cell word (FP32) or positions (FP64) of this thread's next particle
+  int32_t ncell = -1;
+  R npos[3] = {R(-1), R(-1), R(-1)};
+  auto prefetch = [&](int32_t lp) {
+    if (pl.list || lp >= ch.end) return;
+    if constexpr (sizeof(R) == 4) {
+      ncell = *at_byte(q.cell, (uint32_t)lp * 4u);
+    } else {
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) npos[d] = *at_byte(q.pos[d], (uint32_t)lp * 8u);
+    }
+  };
+  prefetch(ch.beg + tid);
   for (int32_t base = ch.beg; base < ch.end; base += bd) {
     const int32_t lp = base + tid;
     const bool ok = lp < ch.end;
+    const int next = turn == 2 ? 0 : turn + 1;
     int32_t slot = lp;
-    if (pl.list && ok) slot = (int32_t)(gp(pl.list)[lp] & 0xffffffffull);
     bool alive = false;
     int c[3] = {0, 0, 0};
-    if (ok) alive = pl.rec ? rec_cell<R, DIM>(q, pl.rec, lp, c) : load_cell<R, DIM>(q, slot, c);
+    if (ok) {
+      if (pl.list) {
+        slot = (int32_t)(gp(pl.list)[lp] & 0xffffffffull);
+        alive = pl.rec ? rec_cell<R, DIM>(q, pl.rec, lp, c) : load_cell<R, DIM>(q, slot, c);
+      } else {
+        alive = decode_cell<R, DIM>(q, ncell, npos, c);
+      }
+    }
+    prefetch(lp + bd);
     int a[3];
     const bool inside = alive && on_chip<DIM>(c, g, n, a);
     const bool gone = alive && !inside;
     const uint64_t mi = __ballot(inside), me = __ballot(gone);
-    const uint64_t below = (1ull << lane) - 1ull;
-    __syncthreads();                   // the previous round has read the list and wsum
+    int bi = 0, be = 0;
     if (lane == 0) {
-      wsum[wv] = __popcll(mi);
-      wsum[nw + wv] = __popcll(me);
+      if (mi) bi = atomicAdd(&cnt[turn], __popcll(mi));
+      if (me) be = atomicAdd(&cnt[3 + turn], __popcll(me));
     }
+    bi = uniform(bi);
+    be = uniform(be) + pend + __popcll(me & below);
+    if (inside) list[side * bd + bi + __popcll(mi & below)] = (uint16_t)tid;
+    if (gone && be < room) wait[be] = slot;
+    escape_append<R, DIM, false>(out, gone && be >= room, seg, slot, q, r, s);
+    if (tid < 2) cnt[3 * tid + next] = 0;
     __syncthreads();
-    if (tid == 0) {
-      int ti = 0, te = 0;
-      for (int w = 0; w < nw; ++w) {
-        const int vi = wsum[w], ve = wsum[nw + w];
-        wsum[w] = ti;
-        wsum[nw + w] = te;
-        ti += vi;
-        te += ve;
-      }
-      wsum[2 * nw] = ti;
-      wsum[2 * nw + 1] = te;
-      wsum[2 * nw + 2] = te ? (int32_t)atomicAdd(esc.count, (unsigned int)te) : 0;
+    const int n_in = uniform(cnt[turn]);
+    pend += uniform(cnt[3 + turn]);
+    if (pend >= room / 2) {
+      flush_waiting<R, DIM>(esc, wait, min(pend, room), gbase, seg, q, r, s);
+      pend = 0;
     }
-    __syncthreads();
-    if (inside) cin[wsum[wv] + __popcll(mi & below)] = pl.rec ? lp : slot;
-    if (gone) cbuf[bd - 1 - (wsum[nw + wv] + __popcll(me & below))] = slot;
-    __syncthreads();
-    const int n_in = wsum[2 * nw], n_esc = wsum[2 * nw + 1];
-    const int64_t ebase = (int64_t)(uint32_t)wsum[2 * nw + 2];
-    for (int e = tid; e < n_esc; e += bd)
-      if (ebase + e < esc.capacity) {
-        const int32_t es = cbuf[bd - 1 - e];
-        esc.items[ebase + e] = ((unsigned long long)seg << 32) | (unsigned long long)(uint32_t)es;
-        if (esc.rec) escape_record<R, DIM>(esc, ebase + e, r, s, q, es);
-      }
     bool late = false;                 // on chip by its cell, not by its own path
     int32_t p = 0;
     if (tid < n_in) {
-      const int32_t src = cin[tid];
+      const int32_t src = base + (int32_t)list[side * bd + tid];
       PState<R> ps;
-      if (pl.rec) {
+      if (pl.list) {
         p = (int32_t)(gp(pl.list)[src] & 0xffffffffull);
-        decode_particle<R, DIM>(q, words_of(load_rec<R>(pl.rec, src)), ps);
+        if (pl.rec) decode_particle<R, DIM>(q, words_of(load_rec<R>(pl.rec, src)), ps);
+        else load_particle<R, DIM>(q, p, ps);
       } else {
         p = src;
         load_particle<R, DIM>(q, p, ps);
@@ -493,8 +535,21 @@ __device__ __forceinline__ double process_chunk_compact(
       late = !push_on_chip<R, DIM, ORDER>(r, g, L, n, b, ps, k, q, p, with_rho, want_ke, ke,
                                           true);
     }
-    escape_append<R, DIM, false>(out, late, seg, p, q, r, s);
+    // late ones wait too, counted with the next round
+    const uint64_t ml = __ballot(late);
+    if (ml) {
+      int bl = 0;
+      if (lane == 0) bl = atomicAdd(&cnt[3 + next], __popcll(ml));
+      bl = uniform(bl) + pend + __popcll(ml & below);
+      if (late && bl < room) wait[bl] = p;
+      escape_append<R, DIM, false>(out, late && bl >= room, seg, p, q, r, s);
+    }
+    turn = next;
+    side ^= 1;
   }
+  __syncthreads();
+  pend += uniform(cnt[3 + turn]);
+  if (pend) flush_waiting<R, DIM>(esc, wait, min(pend, room), gbase, seg, q, r, s);
   return ke * s.m;
 }
 
@@ -705,8 +760,12 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
   L.st = st;
   L.jfold = 1.0f;
 
-  // (2D: the LDS list takes the launch's LDS after the current planes, up to list_end)
-  EscapeOut out{esc, &kept, (unsigned long long*)cbuf, (list_end - (int)((unsigned char*)cbuf - smem_raw)) / 8, 0};
+  // (the lists take the launch's LDS after the current planes, up to list_end)
+  const int left = list_end - (int)((unsigned char*)cbuf - smem_raw);
+  EscapeOut out{esc, &kept, (unsigned long long*)cbuf,
+                left / 8, 0};
+  if constexpr (DIM == 3)
+    out.cap = G ? ROUND_ESC : min(ROUND_ESC, left / 4 - round_words(fused_block<R, DIM, G>(), 0));
   if (threadIdx.x == 0) kept = 0;   // (staging's barrier comes before the first append)
   bool by_four = false;
   if constexpr (DIM == 2) {
@@ -1037,16 +1096,18 @@ size_t fused_smem_bytes(int prec, int dim, int tx, int ty, int tz, int halo, int
   // two charge planes)
   const int jplanes = 3 + charge_planes(with_rho);
   static_assert((6 * sizeof(float)) % 8 == 0, "current planes must start 8-byte aligned");
-  // 3D: the round compaction's slot list and wave sums (process_chunk_compact), sized for
-  // the workgroup of this precision and geometry
+  // 3D: the lists of the compacted rounds (process_chunk_compact), sized for the workgroup of
+  // this precision and geometry
   const int block = geo == 7 || geo == 8
                         ? (prec == 0 ? fused_block<float, 3, 7>() : fused_block<double, 3, 7>())
                         : (prec == 0 ? fused_block<float, 3, 0>() : fused_block<double, 3, 0>());
   const size_t planes = plane * 6 * (prec == 0 ? 4 : 8) + plane * jplanes * 8;
-  // 2D: the list of escaped particles, where the planes leave room for it
+  // the lists of escaped particles (2D of the tile, 3D of the rounds) take what the planes
+  // leave, up to their size
   constexpr size_t room = 160 * 1024 - 512;
-  const size_t list = planes + 8 * FUSED_LIST <= room ? 8 * FUSED_LIST : (planes < room ? room - planes : 0);
-  return planes + (dim == 3 ? ((size_t)block + 64) * 4 : list / 8 * 8);
+  const size_t least = planes + (dim == 3 ? (size_t)round_words(block, geo ? ROUND_ESC : ROUND_ESC_MIN) * 4 : 0);
+  const size_t most = planes + (dim == 3 ? (size_t)round_words(block, ROUND_ESC) * 4 : 8 * FUSED_LIST);
+  return std::max(least, std::min(most, room) / 8 * 8);
 }
 
 }  // namespace lpic
