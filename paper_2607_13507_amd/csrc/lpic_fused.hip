@@ -410,16 +410,22 @@ __device__ __forceinline__ bool push_on_chip(const RunDesc& r, const Region& g, 
 }
 
 // 3D rounds with compaction (one particle per thread per round): each thread first reads
-// only its particle's cell and classifies it (on chip / escaped / none); the on-chip
-// particles of the workgroup are then packed into the first threads (their places in the
-// round pass through LDS) and pushed there, so no wave carries idle lanes for escaped
-// particles.  One barrier per round: the list of a round and its counts (three, taken in
-// turn) are not written again before every wave has passed the next barrier.  The cells of
-// the next round are loaded while this one is pushed.  Escaped particles wait in LDS and go
-// to the escape list by the hundred: a reservation per round kept every round waiting for a
-// global atomic and for the loads of a few records.  (Three barriers and a reservation per
-// round, then one: 256^3 FP32, 134M particles, 368.3 and 355.6 ms per 20 steps.)
+// only its particle's cell and classifies it (on chip / escaped / none); the places of the
+// on-chip ones go into a ring in LDS, and as soon as it holds one for every thread they are
+// pushed, so no lane idles for escaped particles however many there are.  One barrier per
+// round: its counts (three sets, taken in turn) and its places in the ring are not written
+// again before every wave has passed the next barrier.  The cells of the next round are loaded
+// while this one is pushed.  Escaped particles wait in LDS and go to the escape list by the
+// hundred: a reservation per round kept every round waiting for a global atomic and for the
+// loads of a few records.  What bounds it now is the body itself: LDS 67% and the vector units
+// 65% of the busy cycles, half of the LDS cycles bank conflicts of random positions.
+// 20 steps of 256^3 FP32, 134M particles: three barriers and a reservation per round 369 ms,
+// one barrier 355, with the ring instead of a push per round 347 (100 x 84 x 60 FP64, 10
+// steps: 9.76, 9.74, 9.54 ms).  768 instead of 512 threads in FP64 (three waves per SIMD, 168
+// VGPRs): 9.37 ms, but 9.8 instead of 9.2 right after a sort, where the 1024 particles of a
+// tile make two full rounds of 512.
 constexpr int ROUND_ESC = 256;
+constexpr int ROUNDS = 64;   // of up to 1024 threads: places of 16 bits
 
 // LDS of the rounds, in words, for a workgroup of bd threads and `wait` waiting particles:
 // ROUND_ESC in the fixed geometries (all fit), with runtime strides what the planes leave, at
@@ -444,7 +450,7 @@ __device__ __forceinline__ void flush_waiting(const EscapeList& esc, const int32
   __syncthreads();                     // the list and gbase may be written again
 }
 
-template <typename R, int DIM, int ORDER, class LA>
+template <typename R, int DIM, int ORDER, int BD, class LA>
 __device__ __forceinline__ double process_chunk_compact(
     const RunDesc& r, const SegDesc& s, int seg, const Chunk& ch, const Region& g, const LA& L,
     int with_rho, bool want_ke, const EscapeOut& out, const PassList& pl, int32_t* cbuf) {
@@ -452,19 +458,24 @@ __device__ __forceinline__ double process_chunk_compact(
   const int n[3] = {r.nx, r.ny, r.nz};
   const PushConst<R> k = push_const<R>(r, s);
   const PartPtrs<R> q = part_ptrs<R>(s, r);
-  const int bd = (int)blockDim.x, tid = (int)threadIdx.x;
+  const int tid = (int)threadIdx.x;
   const int lane = __lane_id();
   const uint64_t below = (1ull << lane) - 1ull;
-  uint16_t* list = (uint16_t*)cbuf;    // two lists of bd places
+  uint16_t* list = (uint16_t*)cbuf;    // a ring of 2 BD places in the present ROUNDS rounds
   const int room = out.cap;            // escaped slots that may wait
-  int32_t* cnt = cbuf + bd;            // [0..2] on chip, [3..5] escaped, by round modulo 3
+  int32_t* cnt = cbuf + BD;            // [0..2] on chip, [3..5] escaped, by round modulo 3
   int32_t* gbase = cnt + 6;
   int32_t* wait = cnt + 8;
   if (tid < 6) cnt[tid] = 0;
   __syncthreads();
   double ke = 0.0;
   int pend = 0;                        // escaped particles waiting (uniform)
-  int turn = 0, side = 0;
+  int turn = 0;
+  int head = 0, tot = 0;               // the ring: first place taken and how many (uniform)
+  int32_t from = ch.beg;               // what its places count from
+  auto place = [](int i) {             // (i < 4 BD)
+    return (BD & (BD - 1)) == 0 ? i & (2 * BD - 1) : (i < 2 * BD ? i : i - 2 * BD);
+  };
   // the cell word (FP32) or positions (FP64) of this thread's next particle
   int32_t ncell = -1;
   R npos[3] = {R(-1), R(-1), R(-1)};
@@ -478,7 +489,7 @@ __device__ __forceinline__ double process_chunk_compact(
     }
   };
   prefetch(ch.beg + tid);
-  for (int32_t base = ch.beg; base < ch.end; base += bd) {
+  for (int32_t base = ch.beg; base < ch.end; base += BD) {
     const int32_t lp = base + tid;
     const bool ok = lp < ch.end;
     const int next = turn == 2 ? 0 : turn + 1;
@@ -493,7 +504,7 @@ __device__ __forceinline__ double process_chunk_compact(
         alive = decode_cell<R, DIM>(q, ncell, npos, c);
       }
     }
-    prefetch(lp + bd);
+    prefetch(lp + BD);
     int a[3];
     const bool inside = alive && on_chip<DIM>(c, g, n, a);
     const bool gone = alive && !inside;
@@ -505,47 +516,56 @@ __device__ __forceinline__ double process_chunk_compact(
     }
     bi = uniform(bi);
     be = uniform(be) + pend + __popcll(me & below);
-    if (inside) list[side * bd + bi + __popcll(mi & below)] = (uint16_t)tid;
+    if (inside) list[place(head + tot + bi + __popcll(mi & below))] = (uint16_t)(lp - from);
     if (gone && be < room) wait[be] = slot;
     escape_append<R, DIM, false>(out, gone && be >= room, seg, slot, q, r, s);
     if (tid < 2) cnt[3 * tid + next] = 0;
     __syncthreads();
-    const int n_in = uniform(cnt[turn]);
+    tot += uniform(cnt[turn]);
     pend += uniform(cnt[3 + turn]);
     if (pend >= room / 2) {
       flush_waiting<R, DIM>(esc, wait, min(pend, room), gbase, seg, q, r, s);
       pend = 0;
     }
-    bool late = false;                 // on chip by its cell, not by its own path
-    int32_t p = 0;
-    if (tid < n_in) {
-      const int32_t src = base + (int32_t)list[side * bd + tid];
-      PState<R> ps;
-      if (pl.list) {
-        p = (int32_t)(gp(pl.list)[src] & 0xffffffffull);
-        if (pl.rec) decode_particle<R, DIM>(q, words_of(load_rec<R>(pl.rec, src)), ps);
-        else load_particle<R, DIM>(q, p, ps);
-      } else {
-        p = src;
-        load_particle<R, DIM>(q, p, ps);
+    const bool last = base + BD >= ch.end || base + BD - from >= ROUNDS * BD;
+    while (tot >= BD || (last && tot > 0)) {
+      const int m = min(tot, BD);
+      int32_t src = 0;
+      if (tid < m) src = from + (int32_t)list[place(head + tid)];
+      // more than BD taken: the next round's places may be these
+      if (tot > BD) __syncthreads();
+      head = place(head + m);
+      tot -= m;
+      bool late = false;               // on chip by its cell, not by its own path
+      int32_t p = src;
+      if (tid < m) {
+        PState<R> ps;
+        if (pl.list) {
+          p = (int32_t)(gp(pl.list)[src] & 0xffffffffull);
+          if (pl.rec) decode_particle<R, DIM>(q, words_of(load_rec<R>(pl.rec, src)), ps);
+          else load_particle<R, DIM>(q, p, ps);
+        } else {
+          load_particle<R, DIM>(q, p, ps);
+        }
+        int b[3];
+        (void)on_chip<DIM>(ps.c, g, n, b);
+        // always tested: skipping the tests for deep waves costs the 3D body a spilled
+        // register
+        late = !push_on_chip<R, DIM, ORDER>(r, g, L, n, b, ps, k, q, p, with_rho, want_ke, ke,
+                                            true);
       }
-      int b[3];
-      (void)on_chip<DIM>(ps.c, g, n, b);
-      // always tested: skipping the tests for deep waves costs the 3D body a spilled register
-      late = !push_on_chip<R, DIM, ORDER>(r, g, L, n, b, ps, k, q, p, with_rho, want_ke, ke,
-                                          true);
+      // late ones wait too, counted with the next round
+      const uint64_t ml = __ballot(late);
+      if (ml) {
+        int bl = 0;
+        if (lane == 0) bl = atomicAdd(&cnt[3 + next], __popcll(ml));
+        bl = uniform(bl) + pend + __popcll(ml & below);
+        if (late && bl < room) wait[bl] = p;
+        escape_append<R, DIM, false>(out, late && bl >= room, seg, p, q, r, s);
+      }
     }
-    // late ones wait too, counted with the next round
-    const uint64_t ml = __ballot(late);
-    if (ml) {
-      int bl = 0;
-      if (lane == 0) bl = atomicAdd(&cnt[3 + next], __popcll(ml));
-      bl = uniform(bl) + pend + __popcll(ml & below);
-      if (late && bl < room) wait[bl] = p;
-      escape_append<R, DIM, false>(out, late && bl >= room, seg, p, q, r, s);
-    }
+    if (last) from = base + BD;
     turn = next;
-    side ^= 1;
   }
   __syncthreads();
   pend += uniform(cnt[3 + turn]);
@@ -553,7 +573,7 @@ __device__ __forceinline__ double process_chunk_compact(
   return ke * s.m;
 }
 
-template <typename R, int DIM, int ORDER, bool DIRECT, bool KEEP, class LA>
+template <typename R, int DIM, int ORDER, int BD, bool DIRECT, bool KEEP, class LA>
 __device__ __forceinline__ double process_chunk(const RunDesc& r, const SegDesc& s, int seg,
                                                 const Chunk& ch, const Region& g,
                                                 const LA& L, int with_rho,
@@ -565,7 +585,7 @@ __device__ __forceinline__ double process_chunk(const RunDesc& r, const SegDesc&
   // there the records are loaded directly, one memory latency and no barriers per round
   if constexpr (DIM == 3)
     if (!(DIRECT && pl.rec))
-      return process_chunk_compact<R, DIM, ORDER>(r, s, seg, ch, g, L, with_rho, want_ke, out,
+      return process_chunk_compact<R, DIM, ORDER, BD>(r, s, seg, ch, g, L, with_rho, want_ke, out,
                                                   pl, cbuf);
   (void)cbuf;
   const int n[3] = {r.nx, r.ny, r.nz};
@@ -817,8 +837,8 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
     const RunDesc r = run_of(T, s.run);
     const bool want_ke = kinetic || ke_to_diag;
     ke += s.order == 1
-              ? process_chunk<R, DIM, 1, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf, by_four)
-              : process_chunk<R, DIM, 2, (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf, by_four);
+              ? process_chunk<R, DIM, 1, fused_block<R, DIM, G>(), (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf, by_four)
+              : process_chunk<R, DIM, 2, fused_block<R, DIM, G>(), (G >= 7), KEEP>(r, s, ch.seg, ch, g, L, with_rho, want_ke, out, pl, cbuf, by_four);
   }
   const RunDesc& rl = run_of(T, cur_run);
   ke += drain_escapes<R, DIM, KEEP>(T, cur_seg, out, with_rho);

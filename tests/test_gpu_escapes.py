@@ -27,6 +27,7 @@ CASES = [  # ndim, nx, ny, ppc, order, share of the particles moved away
 ROUNDS = [(3, 16, 0, 27, order, share, tile) for order, share, tile in [
     (2, 0.002, (8, 4, 4, 3)), (1, 0.2, (8, 4, 4, 3)), (2, 1.0, (8, 4, 4, 3)), (2, 0.1, (8, 4, 4, 4)),
     (2, 0.3, (4, 4, 4, 3)), (1, 0.03, (4, 8, 4, 3))]]
+ROUNDS.append((3, 16, 0, 343, 2, 0.3, (8, 4, 4, 3)))   # more than 64 rounds of 512 in a chunk
 
 
 @pytest.mark.parametrize("prec", [L.F64_ABS, L.F32_CELLOFS], ids=["f64", "f32"])
@@ -45,7 +46,7 @@ def test_escaped_particles(prec, ndim, nx, ny, ppc, order, share, tile):
     alt = a.like()
     t = L.Tiling(16, 16, 1, 5, 1024, 0) if ndim == 2 else L.Tiling(8, 4, 4, 3, 1024, 0)
     if tile:
-        t = L.Tiling(*tile, 5000, 0)
+        t = L.Tiling(*tile, 50000, 0)
     off = torch.empty(L.lpic_num_tiles(grid, t) + 2, dtype=torch.int32, device="cuda")
     size = L.lpic_sort_ws_bytes(grid, t, n)
     ws = torch.empty(size, dtype=torch.uint8, device="cuda")
