@@ -1026,11 +1026,21 @@ static void launch_fused_d(int geo, const Tables& T, int nblocks, size_t smem,
 #undef LPIC_GEO
 }
 
+// LDS of an escape workgroup: 2D three a CU.  3D one: 256 escaped particles of a few 8 x 4 x 4
+// tiles need about 18 nodes per axis, and a box of 13 (52 KB) leaves most of them to global
+// atomics.  62 x 73 x 51 FP32, 5 a cell, one step: 52 KB and 128 workgroups 623 us, 150 KB 622,
+// with 256 workgroups 565, 75 KB and 256 577 (99 x 75 x 15, 8 a cell, 10 steps: 2809, 2815,
+// 2656, 2671).  Below 128K slots 128, for the empty lists of short steps.
+static int escape_smem(int dim) { return (dim == 3 ? 150 : 52) * 1024; }
+static int escape_blocks(int dim, int64_t slots) {
+  if (dim == 3 && slots > 131072) return 2 * ESCAPE_BLOCKS;
+  return (int)std::min<int64_t>(ESCAPE_BLOCKS, (slots + 255) / 256);
+}
+
 template <typename R, int D>
 static void launch_escape(const Tables& T, int with_rho, double* kinetic, int ke_to_diag,
                           const EscapeList& esc, int skip_at, int blocks, hipStream_t st) {
-  // LDS per workgroup: three workgroups a CU
-  const int smem = 52 * 1024;
+  const int smem = escape_smem(D);
   k_escape<R, D><<<blocks, 256, smem, st>>>(T, with_rho, kinetic, ke_to_diag, esc, skip_at,
                                             smem / 8 / (3 + charge_planes(with_rho)));
 }
@@ -1059,7 +1069,7 @@ void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size
     LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, rb->esc2, 0x7fffffff,
                                             ESCAPE_BLOCKS, st)));
   } else {
-    const int blocks = (int)std::min<int64_t>(ESCAPE_BLOCKS, (esc.capacity + 255) / 256);
+    const int blocks = escape_blocks(dim, esc.capacity);
     LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, 0x7fffffff,
                                             blocks, st)));
   }
@@ -1073,6 +1083,10 @@ static hipError_t set_smem(size_t smem, size_t smem_occ, int* blocks_per_cu) {
     if (e == hipSuccess)
       e = hipFuncSetAttribute((const void*)k_fused<R, D, G, true>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if constexpr (D == 3)
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)k_escape<R, D>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, escape_smem(D));
   if (e != hipSuccess) return e;
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_fused<R, D, G, false>,
                                                       fused_block<R, D, G>(),
