@@ -1039,8 +1039,8 @@ static int escape_blocks(int dim, int64_t slots) {
 
 template <typename R, int D>
 static void launch_escape(const Tables& T, int with_rho, double* kinetic, int ke_to_diag,
-                          const EscapeList& esc, int skip_at, int blocks, hipStream_t st) {
-  const int smem = escape_smem(D);
+                          const EscapeList& esc, int skip_at, int blocks, int smem,
+                          hipStream_t st) {
   k_escape<R, D><<<blocks, 256, smem, st>>>(T, with_rho, kinetic, ke_to_diag, esc, skip_at,
                                             smem / 8 / (3 + charge_planes(with_rho)));
 }
@@ -1064,14 +1064,18 @@ void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size
                                              rb->esc2, false, 0, jshift,
                                              PassList{rb->items, esc.rec ? rb->rec : nullptr},
                                              st)));
+    // (a list below the threshold is a short one for as many workgroups, and needs no LDS; the
+    // second pass's list is normally empty: 128 workgroups with their boxes of LDS cost a step
+    // of 2D or 3D some 4 us)
+    const int few = (rb->threshold + ESCAPE_FEW - 1) / ESCAPE_FEW;
     LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, rb->threshold,
-                                            ESCAPE_BLOCKS, st)));
+                                            few, 0, st)));
     LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, rb->esc2, 0x7fffffff,
-                                            ESCAPE_BLOCKS, st)));
+                                            few, escape_smem(2), st)));
   } else {
     const int blocks = escape_blocks(dim, esc.capacity);
     LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, 0x7fffffff,
-                                            blocks, st)));
+                                            blocks, escape_smem(dim), st)));
   }
 }
 
