@@ -636,13 +636,17 @@ __device__ __forceinline__ double process_chunk(const RunDesc& r, const SegDesc&
 // Empties the workgroup's list at the end of a tile (KEEP: of a tile's species): KEEP pushes
 // the particles (their kinetic energy is returned), otherwise they move to the shared list in
 // one piece.
-// Every thread calls it; the first barrier stands whatever the count.
+// Every thread calls it; the first barrier stands whatever the count.  Between the read of the
+// count and the next append lies a barrier on every way out: on the early return the one of
+// the next tile's staging or, for KEEP, whose species may change within a tile (nothing is
+// staged then), the one right after the read; otherwise the last one here.
 template <typename R, int DIM, bool KEEP>
 __device__ __forceinline__ double drain_escapes(const Tables& T, int seg, const EscapeOut& out,
                                                 int with_rho) {
   __syncthreads();
   if constexpr (DIM == 3) return 0.0;
   const int n = *out.count;
+  if constexpr (KEEP) __syncthreads();
   if (n == 0) return 0.0;
   double ke = 0.0;
   if constexpr (KEEP) {

@@ -13,7 +13,7 @@ import torch
 from gpu_helpers import banner
 from paper_2607_13507_amd import lpic as L
 from paper_2607_13507_amd import workloads as W
-from paper_2607_13507_amd.simulation import DeviceFields, DeviceSpecies, grid_struct
+from paper_2607_13507_amd.simulation import DeviceFields, DeviceSpecies, Simulation, grid_struct
 
 pytestmark = pytest.mark.gpu
 CURRENT = ("jx", "jy", "jz")
@@ -132,3 +132,72 @@ def test_stream_in_cell_order(prec, nx, ny, ppc, order, chunk):
         assert np.abs(f[k] - g[k]).max() <= tol * np.abs(g[k]).max(), k
     for k in ("ux", "uy", "uz"):
         assert np.abs(a.numpy(k) - b.numpy(k)).max() <= ptol, k
+
+
+def _two_species(nx, ny, ppc, orders, seed):
+    wl = W.thermal_2d(nx=nx, ny=ny, dx=0.1, ppc=ppc, T=0.3, order=orders[0], seed=seed)
+    ions = W.thermal_2d(nx=nx, ny=ny, dx=0.1, ppc=ppc, T=0.3, order=orders[1], seed=seed + 1)
+    ions.species[0].q, ions.species[0].m = 1.0, 4.0
+    wl.species.append(ions.species[0])
+    wl.fields = W.random_fields(wl.ncell, seed + 2, 0.5)
+    return wl
+
+
+@pytest.mark.parametrize("prec", [L.F64_ABS, L.F32_CELLOFS], ids=["f64", "f32"])
+@pytest.mark.parametrize("nx,ny", [(256, 192), (288, 256)], ids=["own", "list"])
+def test_escapes_of_two_species(nx, ny, prec):
+    """Two boxes of two species each (different orders), several chunks of a tile and a species
+    per workgroup: a share of one species of a tile moved away, then of both, with diagnostics.
+    `own`: 912,384 slots, pushed by the workgroup that meets them, which empties its list when
+    the species changes inside a tile; `list`: 1,354,752 slots, the shared list."""
+    banner(f"escapes of two species {nx}x{ny} prec={prec}")
+    wls = [_two_species(nx, ny, 9, (2, 1), 51), _two_species(48, 32, 9, (1, 2), 54)]
+
+    def sim():
+        return Simulation(wls, prec=prec, tiling=(16, 16, 1), halo=5, chunk=256,
+                          sort_interval=1000, diag_interval=1, use_graph=False)
+    a, b = sim(), sim()
+    b.register_hook("INTERPOLATOR", lambda *_: 0)      # the split path
+    a.step(1)
+    b.step(1)
+    rng = np.random.default_rng(7)
+    tol, ptol = (1e-11, 1e-12) if prec == L.F64_ABS else (2e-5, 2e-6)
+    for moved in ((0, 3), (0, 1, 2, 3)):
+        e0 = a.stats()["halo_escapes"]
+        away = 0
+        for i in moved:
+            s, g = a.current(i), a.grids[a.species_run[i]]
+            move = rng.random(s.n) < 0.3
+            away += int(move.sum())
+            pos = s.positions(g)
+            for d, box in enumerate((g.nx * g.dx, g.ny * g.dy)):
+                p = pos[d] + 0.5 * box * move
+                pos[d] = np.where(p >= box, p - box, p)
+            s.load_positions(g, pos[0], pos[1])
+        for i in range(4):                             # the same slots in both
+            for k, v in a.current(i).a.items():
+                b.current(i).a[k].copy_(v)
+        for r in range(2):
+            for k, v in a.fields[r].t.items():
+                b.fields[r].t[k].copy_(v)
+        a.step(1)
+        b.step(1)
+        torch.cuda.synchronize()
+        assert a.stats()["fused"] and not b.stats()["fused"]
+        assert a.stats()["halo_escapes"] - e0 >= 0.5 * away, moved
+        for r in range(2):
+            f, g = a.fields[r].numpy(), b.fields[r].numpy()
+            for k in g:
+                assert np.abs(f[k] - g[k]).max() <= tol * np.abs(g[k]).max(), (moved, r, k)
+            ka, kb = (x.diagnostics(r)["kinetic_energy"] for x in (a, b))
+            assert abs(ka - kb) <= (1e-11 if prec == L.F64_ABS else 1e-6) * kb, (moved, r)
+        for i in range(4):
+            sa, sb, g = a.current(i), b.current(i), a.grids[a.species_run[i]]
+            for d, box in enumerate((g.nx * g.dx, g.ny * g.dy)):
+                e = sa.positions(g)[d] - sb.positions(g)[d]
+                assert np.abs(e - box * np.round(e / box)).max() <= ptol * box, (moved, i, d)
+            for k in ("ux", "uy", "uz"):
+                ua, ub = sa.numpy(k).astype(np.float64), sb.numpy(k).astype(np.float64)
+                assert np.abs(ua - ub).max() <= ptol * max(1.0, np.abs(ub).max()), (moved, i, k)
+    a.close()
+    b.close()
