@@ -871,7 +871,8 @@ struct lpic_sim {
   unsigned int* esc2_count = nullptr;         // its counters (and a total)
   int blocks_per_cu = 1;       // fused workgroups resident per CU (without / with charge planes)
   int blocks_per_cu_rho = 1;
-  // fused 2D field update between steps (launch_yee_mid); mid_tx == 0: not in use
+  // fused 2D field update between steps (launch_yee_mid): its tile, 0 where the updates run as
+  // separate kernels; it runs between steps without diagnostics while set2 is there
   int mid_tx = 0, mid_ty = 0, mid_ntiles = 0;
   bool mid_divides = false;                  // the tile divides every box
   bool rows = false;                         // every box satisfies yee_rows
@@ -909,6 +910,32 @@ void drop_graphs(lpic_sim* s) {
     if (s->gexec[i]) (void)hipGraphExecDestroy(s->gexec[i]);
     s->gexec[i] = nullptr;
   }
+}
+
+// Gives the second field set back: from then on the field updates run as separate kernels.
+void free_field_set(lpic_sim* s) {
+  if (s->set2) drop_graphs(s);
+  free_dev(s->set2); free_dev(s->runs2_d); free_dev(s->mid_pfx_d);
+  s->set2 = nullptr;
+  s->runs2_d = nullptr;
+  s->mid_pfx_d = nullptr;
+  s->mid_tx = s->mid_ty = s->mid_ntiles = 0;
+}
+
+// Device memory that the simulation cannot do without.  The second field set only saves time:
+// it is given back before such a request fails.
+hipError_t required_memory(lpic_sim* s, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, std::max<size_t>(bytes, 256));
+  if (e != hipSuccess && s->set2) {
+    (void)hipGetLastError();
+    free_field_set(s);
+    e = hipMalloc(p, std::max<size_t>(bytes, 256));
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+  }
+  return e;
 }
 
 bool intermediate_hooks(const lpic_sim* s) {
@@ -958,6 +985,80 @@ size_t pml_psi_bytes(const lpic_grid* g, int cells, int prec) {
 }
 
 size_t lds_of_geometry(const lpic_sim* s, int g);
+
+// The field tile of the fused 2D update between steps and the second field set: taken after
+// everything that the simulation cannot do without, from the memory that this leaves.  A set of
+// the right size is kept.
+lpic_status field_sets(lpic_sim* s) {
+  int tx = MID_MAX_TX, ty = MID_MAX_TY;
+  size_t bytes = 0;
+  const size_t size = s->prec == LPIC_F32_CELLOFS ? 4 : 8;
+  std::vector<int32_t> pfx(1, 0);
+  const bool fused = s->ndim == 2 && !(s->opt.tiling.flags & LPIC_FIELD_SEPARATE);
+  if (fused) {
+    // the largest tile that divides every box, or, where none does, the largest that no box is
+    // narrower than by more than half
+    for (int r = 0; r < s->nruns; ++r) {
+      while (tx >= 8 && s->grids[r].nx % tx) tx >>= 1;
+      while (ty >= 4 && s->grids[r].ny % ty) ty >>= 1;
+    }
+    s->mid_divides = tx >= 8 && ty >= 4;
+    if (!s->mid_divides || s->windows || tx * ty < 256) {
+      // (a tile below 256 cells leaves threads idle and reads half its cells again as halo;
+      // 1000 x 600 cells in FP64: 42 us with 8 x 8 tiles that divide it, 26 with 64 x 16)
+      int nxm = INT_MAX, nym = INT_MAX;
+      for (int r = 0; r < s->nruns; ++r) {
+        nxm = std::min(nxm, (int)s->grids[r].nx);
+        nym = std::min(nym, (int)s->grids[r].ny);
+      }
+      if (!s->mid_divides || (nxm >= 64 && nym >= 16)) {
+        tx = MID_MAX_TX;
+        ty = MID_MAX_TY;
+        while (tx > 8 && 2 * nxm <= tx) tx >>= 1;
+        while (ty > 4 && 2 * nym <= ty) ty >>= 1;
+      }
+    }
+    for (int r = 0; r < s->nruns; ++r) {
+      const lpic_grid& g = s->grids[r];
+      const bool mur = g.open_x && s->pmls[r].cells == 0;
+      pfx.push_back(pfx.back() + ((g.nx + mid_shift(mur, g.nx, tx) + tx - 1) / tx) *
+                                     ((g.ny + ty - 1) / ty));
+      bytes += 9 * align256(ncells(&g) * size);
+    }
+  }
+  void* keep = nullptr;
+  if (fused && s->set2_bytes == bytes) std::swap(keep, s->set2);
+  free_field_set(s);
+  s->set2 = keep;
+  if (!fused) return LPIC_OK;
+  // (a box that leaves no room for a second set keeps the separate kernels)
+  if ((!s->set2 && hipMalloc(&s->set2, bytes) != hipSuccess) ||
+      hipMalloc((void**)&s->mid_pfx_d, sizeof(int32_t) * pfx.size()) != hipSuccess ||
+      hipMalloc((void**)&s->runs2_d, sizeof(RunDesc) * s->nruns) != hipSuccess) {
+    (void)hipGetLastError();
+    free_field_set(s);
+    return LPIC_OK;
+  }
+  s->set2_bytes = bytes;
+  HIPCHK(hipMemcpy(s->mid_pfx_d, pfx.data(), sizeof(int32_t) * pfx.size(),
+                   hipMemcpyHostToDevice));
+  std::vector<RunDesc> runs2(s->runs_h);
+  char* at = (char*)s->set2;
+  for (int r = 0; r < s->nruns; ++r) {
+    runs2[r].psi_half = 1;
+    for (int k = 0; k < 9; ++k) {
+      runs2[r].f[k] = at;
+      at += align256(ncells(&s->grids[r]) * size);
+    }
+  }
+  HIPCHK(hipMemcpy(s->runs2_d, runs2.data(), sizeof(RunDesc) * s->nruns, hipMemcpyHostToDevice));
+  // without species nothing clears the second set's J: it starts and stays zero
+  HIPCHK(hipMemset(s->set2, 0, bytes));
+  s->mid_tx = tx;
+  s->mid_ty = ty;
+  s->mid_ntiles = pfx.back();
+  return LPIC_OK;
+}
 
 lpic_status configure(lpic_sim* s) {
   drop_graphs(s);
@@ -1041,7 +1142,7 @@ lpic_status configure(lpic_sim* s) {
   s->nbins = bin;
   s->max_chunks = maxch;
   // device tables
-  free_dev(s->runs_d); free_dev(s->runs2_d); free_dev(s->segs_d); free_dev(s->run_blk_d);
+  free_dev(s->runs_d); free_dev(s->segs_d); free_dev(s->run_blk_d);
   free_dev(s->seg_blk256_d); free_dev(s->seg_blk_sort_d);
   free_dev(s->counts); free_dev(s->offsets); free_dev(s->cursor); free_dev(s->mult);
   free_dev(s->chunks); free_dev(s->scan_part);
@@ -1050,13 +1151,13 @@ lpic_status configure(lpic_sim* s) {
   s->rb = Rebin{};
   s->rebin = false;
   s->mult = nullptr;
-  s->runs_d = nullptr; s->runs2_d = nullptr; s->segs_d = nullptr; s->run_blk_d = nullptr;
+  s->runs_d = nullptr; s->segs_d = nullptr; s->run_blk_d = nullptr;
   s->seg_blk256_d = s->seg_blk_sort_d = nullptr;
   s->counts = s->offsets = s->cursor = nullptr;
   s->chunks = nullptr;
 #define ALLOC(ptr, bytes)                                                            \
   do {                                                                               \
-    if (hipMalloc((void**)&(ptr), std::max<size_t>(bytes, 256)) != hipSuccess)        \
+    if (required_memory(s, (void**)&(ptr), bytes) != hipSuccess)                       \
       return fail(LPIC_ENOMEM, "device allocation of %zu bytes failed", (size_t)(bytes)); \
   } while (0)
   ALLOC(s->runs_d, sizeof(RunDesc) * s->nruns);
@@ -1104,76 +1205,6 @@ lpic_status configure(lpic_sim* s) {
     HIPCHK(prepare_fused(s->prec, s->ndim, s->geo_chain, lds_of_geometry(s, s->geo_chain),
                          s->smem_chain, &s->blocks_per_cu_chain));
   HIPCHK(hipMemcpy(s->step_dev, &s->step, sizeof(int64_t), hipMemcpyHostToDevice));
-  // fused 2D field update between steps: the largest field tile that divides every box, or,
-  // where none does, the largest that no box is narrower than by more than half
-  free_dev(s->mid_pfx_d);
-  s->mid_pfx_d = nullptr;
-  s->mid_tx = s->mid_ty = s->mid_ntiles = 0;
-  s->mid_divides = false;
-  if (s->ndim == 2 && !(t.flags & LPIC_FIELD_SEPARATE)) {
-    int tx = MID_MAX_TX, ty = MID_MAX_TY;
-    for (int r = 0; r < s->nruns; ++r) {
-      while (tx >= 8 && s->grids[r].nx % tx) tx >>= 1;
-      while (ty >= 4 && s->grids[r].ny % ty) ty >>= 1;
-    }
-    s->mid_divides = tx >= 8 && ty >= 4;
-    if (!s->mid_divides || s->windows || tx * ty < 256) {
-      // (a tile below 256 cells leaves threads idle and reads half its cells again as halo;
-      // 1000 x 600 cells in FP64: 42 us with 8 x 8 tiles that divide it, 26 with 64 x 16)
-      int nxm = INT_MAX, nym = INT_MAX;
-      for (int r = 0; r < s->nruns; ++r) {
-        nxm = std::min(nxm, (int)s->grids[r].nx);
-        nym = std::min(nym, (int)s->grids[r].ny);
-      }
-      if (!s->mid_divides || (nxm >= 64 && nym >= 16)) {
-        tx = MID_MAX_TX;
-        ty = MID_MAX_TY;
-        while (tx > 8 && 2 * nxm <= tx) tx >>= 1;
-        while (ty > 4 && 2 * nym <= ty) ty >>= 1;
-      }
-    }
-    std::vector<int32_t> pfx(1, 0);
-    size_t bytes = 0;
-    const size_t size = s->prec == LPIC_F32_CELLOFS ? 4 : 8;
-    for (int r = 0; r < s->nruns; ++r) {
-      const lpic_grid& g = s->grids[r];
-      const bool mur = g.open_x && s->pmls[r].cells == 0;
-      pfx.push_back(pfx.back() + ((g.nx + mid_shift(mur, g.nx, tx) + tx - 1) / tx) *
-                                     ((g.ny + ty - 1) / ty));
-      bytes += 9 * align256(ncells(&g) * size);
-    }
-    if (!s->set2 || s->set2_bytes != bytes) {
-      free_dev(s->set2);
-      s->set2 = nullptr;
-      // (a box that leaves no room for a second set keeps the separate kernels)
-      if (hipMalloc(&s->set2, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        s->set2 = nullptr;
-      }
-      s->set2_bytes = bytes;
-    }
-    if (s->set2) {
-      ALLOC(s->mid_pfx_d, sizeof(int32_t) * pfx.size());
-      ALLOC(s->runs2_d, sizeof(RunDesc) * s->nruns);
-      HIPCHK(hipMemcpy(s->mid_pfx_d, pfx.data(), sizeof(int32_t) * pfx.size(),
-                       hipMemcpyHostToDevice));
-      std::vector<RunDesc> runs2(s->runs_h);
-      char* at = (char*)s->set2;
-      for (int r = 0; r < s->nruns; ++r) {
-        runs2[r].psi_half = 1;
-        for (int k = 0; k < 9; ++k) {
-          runs2[r].f[k] = at;
-          at += align256(ncells(&s->grids[r]) * size);
-        }
-      }
-      HIPCHK(hipMemcpy(s->runs2_d, runs2.data(), sizeof(RunDesc) * s->nruns, hipMemcpyHostToDevice));
-      // without species nothing clears the second set's J: it starts and stays zero
-      HIPCHK(hipMemset(s->set2, 0, bytes));
-      s->mid_tx = tx;
-      s->mid_ty = ty;
-      s->mid_ntiles = pfx.back();
-    }
-  }
   if (!s->wmax) {
     ALLOC(s->wmax, sizeof(unsigned long long) * fixed_shift_slots() * std::max(1, s->nsegs));
     ALLOC(s->jshift, sizeof(int32_t) * std::max(1, s->nruns));
@@ -1237,10 +1268,10 @@ lpic_status configure(lpic_sim* s) {
     rb.grid[2] = fused_grid(maxch, bpc[2]);
     s->rebin = true;
   }
+#undef ALLOC
   s->need_sort = true;
   s->offsets_valid = false;
-  return LPIC_OK;
-#undef ALLOC
+  return field_sets(s);
 }
 
 void swap_host_buffers(lpic_sim* s) {
@@ -1282,7 +1313,7 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
   if (move) set ^= 1;
   const Tables Tc = sim_tables(s, nullptr, set);
   const Tables Ts = sim_tables(s, s->seg_blk_sort_d, set);
-  const bool mid = s->mid_tx > 0;
+  const bool mid = s->set2 != nullptr;
   const bool rows = s->rows;
   int64_t* clock = s->laser_bpr > 0 ? s->step_dev : nullptr;
   if (diag) {
@@ -1451,7 +1482,7 @@ lpic_status ensure_old_state(lpic_sim* s) {
     s->old_off.push_back(tot);
     tot += align256(old_state_bytes(s->ndim, s->sp[i].n, s->prec));
   }
-  if (hipMalloc(&s->old_state, std::max<size_t>(tot, 256)) != hipSuccess)
+  if (required_memory(s, &s->old_state, tot) != hipSuccess)
     return fail(LPIC_ENOMEM, "old-state allocation of %zu bytes failed", tot);
   return LPIC_OK;
 }
@@ -1529,7 +1560,7 @@ void lpic_sim_destroy(lpic_sim* s) {
   if (!s) return;
   if (s->stream) (void)hipStreamSynchronize(s->stream);
   drop_graphs(s);
-  free_dev(s->runs2_d);
+  free_field_set(s);
   for (auto& e : s->ev_pending) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
   for (auto& e : s->ev_free) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
   free_dev(s->runs_d); free_dev(s->segs_d); free_dev(s->run_blk_d);
@@ -1543,7 +1574,6 @@ void lpic_sim_destroy(lpic_sim* s) {
   free_dev(s->rb_items); free_dev(s->esc2_items); free_dev(s->esc2_count);
   free_dev(s->esc_rec); free_dev(s->rb_rec); free_dev(s->esc_keys);
   free_dev(s->wmax); free_dev(s->jshift); free_dev(s->step_dev);
-  free_dev(s->mid_pfx_d); free_dev(s->set2);
   free_dev(s->old_state);
   for (void* p : s->psi) free_dev(p);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
@@ -1583,7 +1613,7 @@ lpic_status lpic_step(lpic_sim* s, int32_t nsteps) {
   // the field set in use, and whether the first step's updates move to the other one
   int set = 0;
   bool move = false;
-  if (s->mid_tx > 0 && !hooks)
+  if (s->set2 && !hooks)
     for (int n = 0; n + 1 < nsteps; ++n)
       if (s->opt.diag_interval == 0 || ((s->step + n + 1) % s->opt.diag_interval) != 0) move = !move;
   for (int n = 0; n < nsteps; ++n) {
@@ -1628,7 +1658,7 @@ lpic_status lpic_step(lpic_sim* s, int32_t nsteps) {
                        rho, set, move));
     }
     if (move) set ^= 1;
-    if (skip_last && s->mid_tx > 0) set ^= 1;
+    if (skip_last && s->set2) set ^= 1;
     move = false;
     if (do_sort && s->nsegs > 0) {
       ++s->sorts;
@@ -1784,7 +1814,7 @@ lpic_status lpic_set_pml(lpic_sim* s, int32_t r, const lpic_pml* pml) {
     const bool f32 = s->prec == LPIC_F32_CELLOFS;
     std::vector<float> tabf(tab.begin(), tab.end());
     const size_t tab_bytes = tab.size() * (f32 ? 4 : 8);
-    if (hipMalloc(&s->psi[r], psi_bytes + tab_bytes) != hipSuccess)
+    if (required_memory(s, &s->psi[r], psi_bytes + tab_bytes) != hipSuccess)
       return fail(LPIC_ENOMEM, "PML allocation of %zu bytes failed", psi_bytes + tab_bytes);
     HIPCHK(hipMemset(s->psi[r], 0, psi_bytes));
     HIPCHK(hipMemcpy((char*)s->psi[r] + psi_bytes, f32 ? (const void*)tabf.data()

@@ -1,0 +1,139 @@
+"""Simulation set-up and stepping of liblpic.so on the host: its sequence of allocations and
+launches under a stand-in HIP runtime (hip_host_stub.cpp) in a process of its own, where memory
+can run out and a launch can fail at a chosen place without a GPU."""
+import ctypes
+import importlib.util
+import os
+import subprocess
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+PKG = os.path.join(os.path.dirname(HERE), "paper_2607_13507_amd")
+NX, NY, SLOTS = 128, 64, 30000
+
+
+def _child(case, tmp_path):
+    so = str(tmp_path / "stub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7",
+                    "-o", so, os.path.join(HERE, "hip_host_stub.cpp")], check=True)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), case, so], capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+class Host:
+    """The stand-in runtime, the library bound to it, and one 2D FP64 box (its arrays, too, come
+    from the stand-in)."""
+
+    def __init__(self, so):
+        self.stub = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
+        for name, res, args in (("stub_used", ctypes.c_size_t, []),
+                                ("stub_budget", None, [ctypes.c_size_t]),
+                                ("stub_newest", ctypes.c_void_p, [ctypes.c_size_t]),
+                                ("stub_events", ctypes.c_char_p, [])):
+            f = getattr(self.stub, name)
+            f.restype, f.argtypes = res, args
+        spec = importlib.util.spec_from_file_location("lpic", os.path.join(PKG, "lpic.py"))
+        self.L = L = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(L)
+        lib = ctypes.CDLL(L.LIB_PATH)
+        for name, (res, args) in L.EXPORTS.items():
+            getattr(lib, name).restype, getattr(lib, name).argtypes = res, args
+        L._lib = lib
+        self.grid = L.Grid(2, NX, NY, 1, 0.1, 0.1, 1.0, 0.05, 0.0, 0, 0)
+        self.fields = L.Fields(*[self.alloc(NX * NY * 8) for _ in range(11)])
+        self.sp, self.alt = self.species(), self.species()
+
+    def alloc(self, n):
+        p = ctypes.c_void_p()
+        assert self.stub.hipMalloc(ctypes.byref(p), ctypes.c_size_t(n)) == 0
+        return p.value
+
+    def species(self):
+        a = [self.alloc(SLOTS * 8) for _ in range(6)]
+        return self.L.Species(SLOTS, -1.0, 1.0, 2, 0, None, None, None, None, a[0], a[1], None,
+                              *a[2:])
+
+    def create(self, species=True, flags=0, diag=0, graph=True, open_x=False):
+        L = self.L
+        o = L.Options(L.Tiling(16, 16, 1, 5, 256, flags), 10, diag, int(graph), 0)
+        self.grid.open_x = int(open_x)
+        sp, alt = ([self.sp], [self.alt]) if species else ([], [])
+        return L.lpic_sim_create([self.grid], [self.fields], sp, [0] * len(sp), alt, L.F64_ABS, o,
+                                 0)
+
+    def tile(self, h):
+        t = self.L.lpic_get_stats(h).field_tile
+        return t[0], t[1]
+
+    def events(self):
+        return self.stub.stub_events().decode().splitlines()
+
+    def kernels(self):
+        """Names of the launched kernels (template arguments left out), in order."""
+        out = []
+        for e in self.events():
+            if e.startswith("launch "):
+                name = e.split()[1]
+                out.append(name[name.index("k_"):].split("I")[0])
+        return out
+
+
+# ---- the cases, each in a process of its own -------------------------------------------------
+def memory(H):
+    """The second field set takes what the required buffers leave: not created before them, and
+    given back when one that is needed later finds no room."""
+    set2 = 9 * NX * NY * 8
+    u0 = H.stub.stub_used()
+    for flags in (0, H.L.ESCAPE_REBIN):
+        h = H.create(flags=flags | H.L.FIELD_SEPARATE)
+        need = H.stub.stub_used() - u0
+        H.L.lpic_sim_destroy(h)
+        # room for the required memory and all but one byte of the set
+        H.stub.stub_budget(u0 + need + set2 - 1)
+        h = H.create(flags=flags)
+        assert H.tile(h) == (0, 0)
+        H.L.lpic_step(h, 3)
+        assert "k_yee_mid" not in H.kernels()
+        H.L.lpic_sim_destroy(h)
+        H.stub.stub_budget(2 ** 63)
+        h = H.create(flags=flags)
+        assert H.tile(h) == (64, 16)
+        H.kernels()
+        H.L.lpic_step(h, 3)
+        assert H.kernels().count("k_yee_mid") == 2
+        # the split path's buffer: room only where the set is
+        H.stub.stub_budget(H.stub.stub_used())
+        hook = H.L.HOOK_FN(lambda *_: 0)
+        H.L.lpic_register_hook(h, H.L.STAGE["INTERPOLATOR"], hook, None)
+        H.L.lpic_step(h, 2)
+        assert H.tile(h) == (0, 0)
+        H.L.lpic_clear_hooks(h)
+        H.L.lpic_step(h, 3)
+        assert "k_yee_mid" not in H.kernels()
+        H.L.lpic_sim_destroy(h)
+        H.stub.stub_budget(2 ** 63)
+        assert H.stub.stub_used() == u0
+
+
+def layers(H):
+    """PML layers that find no room beside the set."""
+    h = H.create(species=False, open_x=True)
+    assert H.tile(h) == (64, 16)
+    H.stub.stub_budget(H.stub.stub_used())
+    H.L.lpic_set_pml(h, 0, H.L.Pml(8, 3, 1, 0, -1.0, 1.0, 0.0))
+    H.L.lpic_step(h, 3)
+    assert "k_pml" not in H.kernels()
+
+
+# ---- the tests -------------------------------------------------------------------------------
+def test_required_memory_before_the_second_field_set(tmp_path):
+    _child("memory", tmp_path)
+
+
+def test_layers_before_the_second_field_set(tmp_path):
+    _child("layers", tmp_path)
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]](Host(sys.argv[2]))
