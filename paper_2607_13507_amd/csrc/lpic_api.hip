@@ -987,8 +987,9 @@ size_t pml_psi_bytes(const lpic_grid* g, int cells, int prec) {
 size_t lds_of_geometry(const lpic_sim* s, int g);
 
 // The field tile of the fused 2D update between steps and the second field set: taken after
-// everything that the simulation cannot do without, from the memory that this leaves.  A set of
-// the right size is kept.
+// everything that the simulation cannot do without, from the memory that this leaves, and only
+// where a fused update can follow a step (one without diagnostics).  A set of the right size is
+// kept.
 lpic_status field_sets(lpic_sim* s) {
   int tx = MID_MAX_TX, ty = MID_MAX_TY;
   size_t bytes = 0;
@@ -1026,34 +1027,37 @@ lpic_status field_sets(lpic_sim* s) {
       bytes += 9 * align256(ncells(&g) * size);
     }
   }
+  const bool wanted = fused && s->opt.diag_interval != 1;
   void* keep = nullptr;
-  if (fused && s->set2_bytes == bytes) std::swap(keep, s->set2);
+  if (wanted && s->set2_bytes == bytes) std::swap(keep, s->set2);
   free_field_set(s);
   s->set2 = keep;
   if (!fused) return LPIC_OK;
-  // (a box that leaves no room for a second set keeps the separate kernels)
-  if ((!s->set2 && hipMalloc(&s->set2, bytes) != hipSuccess) ||
-      hipMalloc((void**)&s->mid_pfx_d, sizeof(int32_t) * pfx.size()) != hipSuccess ||
-      hipMalloc((void**)&s->runs2_d, sizeof(RunDesc) * s->nruns) != hipSuccess) {
-    (void)hipGetLastError();
-    free_field_set(s);
-    return LPIC_OK;
-  }
-  s->set2_bytes = bytes;
-  HIPCHK(hipMemcpy(s->mid_pfx_d, pfx.data(), sizeof(int32_t) * pfx.size(),
-                   hipMemcpyHostToDevice));
-  std::vector<RunDesc> runs2(s->runs_h);
-  char* at = (char*)s->set2;
-  for (int r = 0; r < s->nruns; ++r) {
-    runs2[r].psi_half = 1;
-    for (int k = 0; k < 9; ++k) {
-      runs2[r].f[k] = at;
-      at += align256(ncells(&s->grids[r]) * size);
+  if (wanted) {
+    // (a box that leaves no room for a second set keeps the separate kernels)
+    if ((!s->set2 && hipMalloc(&s->set2, bytes) != hipSuccess) ||
+        hipMalloc((void**)&s->mid_pfx_d, sizeof(int32_t) * pfx.size()) != hipSuccess ||
+        hipMalloc((void**)&s->runs2_d, sizeof(RunDesc) * s->nruns) != hipSuccess) {
+      (void)hipGetLastError();
+      free_field_set(s);
+      return LPIC_OK;
     }
+    s->set2_bytes = bytes;
+    HIPCHK(hipMemcpy(s->mid_pfx_d, pfx.data(), sizeof(int32_t) * pfx.size(),
+                     hipMemcpyHostToDevice));
+    std::vector<RunDesc> runs2(s->runs_h);
+    char* at = (char*)s->set2;
+    for (int r = 0; r < s->nruns; ++r) {
+      runs2[r].psi_half = 1;
+      for (int k = 0; k < 9; ++k) {
+        runs2[r].f[k] = at;
+        at += align256(ncells(&s->grids[r]) * size);
+      }
+    }
+    HIPCHK(hipMemcpy(s->runs2_d, runs2.data(), sizeof(RunDesc) * s->nruns, hipMemcpyHostToDevice));
+    // without species nothing clears the second set's J: it starts and stays zero
+    HIPCHK(hipMemset(s->set2, 0, bytes));
   }
-  HIPCHK(hipMemcpy(s->runs2_d, runs2.data(), sizeof(RunDesc) * s->nruns, hipMemcpyHostToDevice));
-  // without species nothing clears the second set's J: it starts and stays zero
-  HIPCHK(hipMemset(s->set2, 0, bytes));
   s->mid_tx = tx;
   s->mid_ty = ty;
   s->mid_ntiles = pfx.back();

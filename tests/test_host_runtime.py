@@ -126,6 +126,24 @@ def layers(H):
     assert "k_pml" not in H.kernels()
 
 
+def unused(H):
+    """No second set where no step can use it, and none left over from before."""
+    u0 = H.stub.stub_used()
+    h = H.create(species=False, flags=H.L.FIELD_SEPARATE)
+    need = H.stub.stub_used() - u0
+    H.L.lpic_sim_destroy(h)
+    h = H.create(species=False, diag=1)
+    assert H.tile(h) == (64, 16)
+    assert H.stub.stub_used() - u0 == need
+    H.L.lpic_step(h, 3)
+    assert "k_yee_mid" not in H.kernels()
+    for diag, flags, fused in ((4, 0, True), (4, H.L.FIELD_SEPARATE, False), (1, 0, False)):
+        H.L.lpic_set_options(h, H.L.Options(H.L.Tiling(16, 16, 1, 5, 256, flags), 10, diag, 1, 0))
+        assert (H.stub.stub_used() - u0 > need) == fused, (diag, flags)
+        H.L.lpic_step(h, 3)
+        assert ("k_yee_mid" in H.kernels()) == fused, (diag, flags)
+
+
 # ---- the tests -------------------------------------------------------------------------------
 def test_required_memory_before_the_second_field_set(tmp_path):
     _child("memory", tmp_path)
@@ -133,6 +151,10 @@ def test_required_memory_before_the_second_field_set(tmp_path):
 
 def test_layers_before_the_second_field_set(tmp_path):
     _child("layers", tmp_path)
+
+
+def test_no_second_field_set_where_none_is_used(tmp_path):
+    _child("unused", tmp_path)
 
 
 if __name__ == "__main__":
