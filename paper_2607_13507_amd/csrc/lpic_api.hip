@@ -1055,8 +1055,10 @@ lpic_status field_sets(lpic_sim* s) {
       }
     }
     HIPCHK(hipMemcpy(s->runs2_d, runs2.data(), sizeof(RunDesc) * s->nruns, hipMemcpyHostToDevice));
-    // without species nothing clears the second set's J: it starts and stays zero
-    HIPCHK(hipMemset(s->set2, 0, bytes));
+    // without species nothing clears the second set's J: it starts and stays zero (the rest of
+    // the set is written before it is read)
+    for (int r = 0; s->nsegs == 0 && r < s->nruns; ++r)
+      HIPCHK(hipMemset(runs2[r].f[F_JX], 0, 3 * align256(ncells(&s->grids[r]) * size)));
   }
   s->mid_tx = tx;
   s->mid_ty = ty;
@@ -1275,7 +1277,10 @@ lpic_status configure(lpic_sim* s) {
 #undef ALLOC
   s->need_sort = true;
   s->offsets_valid = false;
-  return field_sets(s);
+  CHK(field_sets(s));
+  // the buffers were cleared on the null stream, which the caller's stream need not wait for
+  HIPCHK(hipStreamSynchronize(nullptr));
+  return LPIC_OK;
 }
 
 void swap_host_buffers(lpic_sim* s) {

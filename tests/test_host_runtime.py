@@ -144,6 +144,40 @@ def unused(H):
         assert ("k_yee_mid" in H.kernels()) == fused, (diag, flags)
 
 
+def clears(H):
+    """What set-up clears on the null stream is there before a call returns: the caller's stream
+    may be one that does not wait for the null stream."""
+    def last_clear_is_waited_for():
+        e = H.events()
+        last = max((i for i, x in enumerate(e) if x == "memset"), default=-1)
+        return last >= 0 and any(x.startswith("wait") for x in e[last + 1:])
+    for species in (False, True):
+        for flags in (0, H.L.FIELD_SEPARATE, H.L.ESCAPE_REBIN):
+            H.events()
+            h = H.create(species=species, flags=flags, open_x=True)
+            assert last_clear_is_waited_for(), (species, flags)
+            H.L.lpic_set_laser(h, 0, H.L.Laser(1, 4, 1.0, 1.0, 1.0, 3.0, 0.0, 0.0, 10.0))
+            assert last_clear_is_waited_for(), (species, flags)
+            H.L.lpic_set_pml(h, 0, H.L.Pml(8, 3, 1, 0, -1.0, 1.0, 0.0))
+            assert last_clear_is_waited_for(), (species, flags)
+            H.L.lpic_sim_destroy(h)
+
+
+def second_set_current(H):
+    """Only a box without species has its second J cleared at set-up (nothing else does it)."""
+    set2 = 9 * NX * NY * 8
+    for species in (False, True):
+        h = H.create(species=species)
+        p = H.stub.stub_newest(set2)
+        ctypes.memset(p, 7, set2)
+        H.L.lpic_set_laser(h, 0, None)                   # reconfigures, keeps the set
+        assert H.stub.stub_newest(set2) == p
+        a = ctypes.string_at(p, set2)
+        assert a[:set2 // 3 * 2] == b"\7" * (set2 // 3 * 2)
+        assert a[set2 // 3 * 2:] == (b"\7" if species else b"\0") * (set2 // 3)
+        H.L.lpic_sim_destroy(h)
+
+
 # ---- the tests -------------------------------------------------------------------------------
 def test_required_memory_before_the_second_field_set(tmp_path):
     _child("memory", tmp_path)
@@ -155,6 +189,14 @@ def test_layers_before_the_second_field_set(tmp_path):
 
 def test_no_second_field_set_where_none_is_used(tmp_path):
     _child("unused", tmp_path)
+
+
+def test_clears_are_done_when_a_call_returns(tmp_path):
+    _child("clears", tmp_path)
+
+
+def test_current_of_the_second_field_set(tmp_path):
+    _child("second_set_current", tmp_path)
 
 
 if __name__ == "__main__":
