@@ -137,7 +137,9 @@ typedef struct {
  * tiles of up to 64 x 16 cells, which computes the same values with one pass over the
  * arrays, between the caller's E, B and J and a second set of the library's own (9 arrays
  * per box, taken last and given back where the simulation itself needs the room; without
- * it the three kernels run).  A call of lpic_step starts and ends on the caller's arrays.
+ * it the three kernels run).  A call of lpic_step starts and ends on the caller's arrays; one
+ * that fails in between copies the fields back to them, and if that fails too, later calls
+ * return LPIC_EHIP.
  * LPIC_ESCAPE_REBIN (lpic_step): when a step finds many particles (at least 4096) whose
  * gather stencil or deposit window leaves the staged region of the tile they were sorted
  * into, group them by the tile they are in now (a count, a scan and a scatter of their

@@ -879,6 +879,7 @@ struct lpic_sim {
   int32_t* mid_pfx_d = nullptr;              // nruns + 1 prefix of field tiles
   void* set2 = nullptr;                      // E, B and J of the second field set
   size_t set2_bytes = 0;
+  bool lost = false;                         // a failed call could not bring the fields back
   void* old_state = nullptr;
   std::vector<size_t> old_off;
   std::vector<HookEntry> hooks[LPIC_NUM_STAGES];
@@ -1309,19 +1310,19 @@ lpic_status enqueue_fixed_shift(lpic_sim* s, hipStream_t st) {
 // array, so E + (dt/2)(curl B - J) twice is E + dt (curl B - J).  With the fused 2D field
 // update the previous step already did all of it (its B half, this full E update and this
 // step's first B half) and cleared J, and this step only clears the charge it accumulates.
-// set: the field set (FieldSets) that holds the fields at the start; the fused update of a
-// step that defers its last E half moves them to the other one.  move: the step's first
-// updates move them too (one call starts and ends on the caller's set, so a call with an odd
-// number of fused updates moves once more).
+// set: the field set (FieldSets) that holds the fields, after each launch that moves them too:
+// the fused update of a step that defers its last E half moves them to the other one.  move:
+// the step's first updates move them as well (one call starts and ends on the caller's set, so
+// a call with an odd number of fused updates moves once more).
 // rho: the charge this step accumulates (deposit's with_rho): 1 on a diagnostic step, or
 // with chained charge 2 on the step before one and 3 on the diagnostic step; 0 otherwise.
 lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread, bool diag,
                          bool eager_hooks, bool capturing, bool first_full, bool skip_last,
-                         int rho, int set, bool move) {
+                         int rho, int& set, bool move) {
   const Tables T0 = sim_tables(s, nullptr, set);
-  if (move) set ^= 1;
-  const Tables Tc = sim_tables(s, nullptr, set);
-  const Tables Ts = sim_tables(s, s->seg_blk_sort_d, set);
+  const int moved = set ^ (move ? 1 : 0);
+  const Tables Tc = sim_tables(s, nullptr, moved);
+  const Tables Ts = sim_tables(s, s->seg_blk_sort_d, moved);
   const bool mid = s->set2 != nullptr;
   const bool rows = s->rows;
   int64_t* clock = s->laser_bpr > 0 ? s->step_dev : nullptr;
@@ -1346,6 +1347,7 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
     CHK(last_launch("yee E"));
     launch_yee(T0, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st, rows, out);
     CHK(last_launch("yee B"));
+    set = moved;
   }
   if (eager_hooks) CHK(run_hooks(s, LPIC_STAGE_MAXWELL_1));
   // sort particles (every sort_interval steps)
@@ -1454,6 +1456,7 @@ lpic_status enqueue_step(lpic_sim* s, hipStream_t st, bool do_sort, bool spread,
     sets.species = s->nsegs > 0;
     launch_yee_mid(Tm, s->prec, s->mid_ntiles, sets, pml, st);
     CHK(last_launch("yee fused"));
+    set ^= 1;
   } else {
     // field half update t + dt/2 -> t + dt (B first)
     launch_yee(Tc, s->prec, s->ndim, s->nblk_cells, 1, 0.5, 0, 1, st, rows);
@@ -1493,6 +1496,109 @@ lpic_status ensure_old_state(lpic_sim* s) {
   }
   if (required_memory(s, &s->old_state, tot) != hipSuccess)
     return fail(LPIC_ENOMEM, "old-state allocation of %zu bytes failed", tot);
+  return LPIC_OK;
+}
+
+// After an error with the fields in the second set: back to the caller's arrays, where a caller
+// and the next call look for them (with the half of psi and the clock word that go with them).
+lpic_status fields_back(lpic_sim* s) {
+  const size_t size = s->prec == LPIC_F32_CELLOFS ? 4 : 8;
+  const char* at = (const char*)s->set2;
+  for (int r = 0; r < s->nruns; ++r) {
+    for (int k = 0; k < 9; ++k) {
+      const size_t n = ncells(&s->grids[r]) * size;
+      HIPCHK(hipMemcpyAsync(s->runs_h[r].f[k], at, n, hipMemcpyDeviceToDevice, s->stream));
+      at += align256(n);
+    }
+    if (s->pmls[r].cells > 0) {
+      const size_t half = pml_psi_bytes(&s->grids[r], s->pmls[r].cells, s->prec) / 2;
+      HIPCHK(hipMemcpyAsync(s->psi[r], (const char*)s->psi[r] + half, half,
+                            hipMemcpyDeviceToDevice, s->stream));
+    }
+  }
+  if (s->laser_bpr > 0)
+    HIPCHK(hipMemcpyAsync(s->step_dev, s->step_dev + 1, sizeof(int64_t),
+                          hipMemcpyDeviceToDevice, s->stream));
+  return LPIC_OK;
+}
+
+// The steps of one lpic_step call.  set: the field set that holds the fields, 0 (the caller's)
+// at the start and, without an error, at the end.
+lpic_status run_steps(lpic_sim* s, int32_t nsteps, int& set) {
+  const bool split = intermediate_hooks(s);
+  if (split) CHK(ensure_old_state(s));
+  const bool use_graph = s->opt.use_graph && !s->timing && !inner_hooks(s);
+  s->last_graph = use_graph;
+  CHK(run_hooks(s, LPIC_STAGE_START));
+  bool shift_known = false;
+  const bool hooks = any_hooks(s);
+  // chained charge inside this call (no hooks, so nothing looks at or moves the particles
+  // between the two steps of a chain)
+  const bool chain = s->chain && !hooks && !split && s->opt.diag_interval >= 2;
+  int prev_rho = 0;
+  bool e_half_pending = false;
+  // whether the first step's updates move the fields to the other set
+  bool move = false;
+  if (s->set2 && !hooks)
+    for (int n = 0; n + 1 < nsteps; ++n)
+      if (s->opt.diag_interval == 0 || ((s->step + n + 1) % s->opt.diag_interval) != 0) move = !move;
+  for (int n = 0; n < nsteps; ++n) {
+    CHK(run_hooks(s, LPIC_STAGE_LOOP_START));
+    const bool do_sort = s->need_sort || (s->step % s->opt.sort_interval) == 0;
+    const bool always_spread = (s->opt.tiling.flags & LPIC_SORT_SPREAD) != 0;
+    const bool spread = do_sort && (s->need_spread || always_spread);
+    const bool diag = s->opt.diag_interval > 0 && ((s->step + 1) % s->opt.diag_interval) == 0;
+    const bool pre_diag = chain && n + 1 < nsteps && ((s->step + 2) % s->opt.diag_interval) == 0;
+    const int rho = diag ? (prev_rho == 2 ? 3 : 1) : (pre_diag ? 2 : 0);
+    prev_rho = rho;
+    // inside one call, with no hooks that could look at the fields between steps, a step
+    // that ends without diagnostics leaves its last E half to the next step
+    const bool first_full = e_half_pending;
+    const bool skip_last = !hooks && !diag && n + 1 < nsteps;
+    e_half_pending = skip_last;
+    if (!shift_known && !any_hooks(s)) {
+      CHK(enqueue_fixed_shift(s, s->stream));
+      shift_known = true;
+    }
+    // the one-off spreading sort runs eagerly; captured sort steps use the plain sort unless
+    // every sort spreads
+    if (use_graph && (!spread || always_spread)) {
+      const int gi = (move ? 128 : 0) + set * 64 + rho * 16 + (do_sort ? 8 : 0) + (diag ? 4 : 0) +
+                     (first_full ? 2 : 0) + (skip_last ? 1 : 0);
+      if (!s->gexec[gi]) {
+        hipGraph_t g = nullptr;
+        HIPCHK(hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
+        int captured = set;
+        lpic_status st = enqueue_step(s, s->cap_stream, do_sort, spread, diag, false, true,
+                                      first_full, skip_last, rho, captured, move);
+        hipError_t ee = hipStreamEndCapture(s->cap_stream, &g);
+        if (st != LPIC_OK) { if (g) (void)hipGraphDestroy(g); return st; }
+        if (ee != hipSuccess) return fail(LPIC_EHIP, "graph capture: %s", hipGetErrorString(ee));
+        hipError_t ie = hipGraphInstantiate(&s->gexec[gi], g, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(g);
+        if (ie != hipSuccess) return fail(LPIC_EHIP, "graph instantiate: %s", hipGetErrorString(ie));
+      }
+      HIPCHK(hipGraphLaunch(s->gexec[gi], s->stream));
+      if (move) set ^= 1;
+      if (skip_last && s->set2) set ^= 1;
+      if (do_sort && s->nsegs > 0) swap_host_buffers(s);
+    } else {
+      CHK(enqueue_step(s, s->stream, do_sort, spread, diag, true, false, first_full, skip_last,
+                       rho, set, move));
+    }
+    move = false;
+    if (do_sort && s->nsegs > 0) {
+      ++s->sorts;
+      s->need_sort = false;
+      s->need_spread = false;
+      std::fill(s->inject_used.begin(), s->inject_used.end(), 0);
+      s->offsets_valid = true;
+    }
+    if (diag) s->diag_step = s->step + 1;
+    ++s->step;
+    CHK(run_hooks(s, LPIC_STAGE_LOOP_END));
+  }
+  CHK(run_hooks(s, LPIC_STAGE_FINISH));
   return LPIC_OK;
 }
 
@@ -1607,81 +1713,16 @@ lpic_status lpic_clear_hooks(lpic_sim* s) {
 lpic_status lpic_step(lpic_sim* s, int32_t nsteps) {
   if (!s) return fail(LPIC_EINVAL, "sim is NULL");
   if (nsteps < 0) return fail(LPIC_EINVAL, "nsteps must be >= 0");
-  const bool split = intermediate_hooks(s);
-  if (split) CHK(ensure_old_state(s));
-  const bool use_graph = s->opt.use_graph && !s->timing && !inner_hooks(s);
-  s->last_graph = use_graph;
-  CHK(run_hooks(s, LPIC_STAGE_START));
-  bool shift_known = false;
-  const bool hooks = any_hooks(s);
-  // chained charge inside this call (no hooks, so nothing looks at or moves the particles
-  // between the two steps of a chain)
-  const bool chain = s->chain && !hooks && !split && s->opt.diag_interval >= 2;
-  int prev_rho = 0;
-  bool e_half_pending = false;
-  // the field set in use, and whether the first step's updates move to the other one
+  if (s->lost) return fail(LPIC_EHIP, "the fields were lost when an earlier call failed");
   int set = 0;
-  bool move = false;
-  if (s->set2 && !hooks)
-    for (int n = 0; n + 1 < nsteps; ++n)
-      if (s->opt.diag_interval == 0 || ((s->step + n + 1) % s->opt.diag_interval) != 0) move = !move;
-  for (int n = 0; n < nsteps; ++n) {
-    CHK(run_hooks(s, LPIC_STAGE_LOOP_START));
-    const bool do_sort = s->need_sort || (s->step % s->opt.sort_interval) == 0;
-    const bool always_spread = (s->opt.tiling.flags & LPIC_SORT_SPREAD) != 0;
-    const bool spread = do_sort && (s->need_spread || always_spread);
-    const bool diag = s->opt.diag_interval > 0 && ((s->step + 1) % s->opt.diag_interval) == 0;
-    const bool pre_diag = chain && n + 1 < nsteps && ((s->step + 2) % s->opt.diag_interval) == 0;
-    const int rho = diag ? (prev_rho == 2 ? 3 : 1) : (pre_diag ? 2 : 0);
-    prev_rho = rho;
-    // inside one call, with no hooks that could look at the fields between steps, a step
-    // that ends without diagnostics leaves its last E half to the next step
-    const bool first_full = e_half_pending;
-    const bool skip_last = !hooks && !diag && n + 1 < nsteps;
-    e_half_pending = skip_last;
-    if (!shift_known && !any_hooks(s)) {
-      CHK(enqueue_fixed_shift(s, s->stream));
-      shift_known = true;
-    }
-    // the one-off spreading sort runs eagerly; captured sort steps use the plain sort unless
-    // every sort spreads
-    if (use_graph && (!spread || always_spread)) {
-      const int gi = (move ? 128 : 0) + set * 64 + rho * 16 + (do_sort ? 8 : 0) + (diag ? 4 : 0) +
-                     (first_full ? 2 : 0) + (skip_last ? 1 : 0);
-      if (!s->gexec[gi]) {
-        hipGraph_t g = nullptr;
-        HIPCHK(hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
-        lpic_status st = enqueue_step(s, s->cap_stream, do_sort, spread, diag, false, true,
-                                      first_full, skip_last, rho, set, move);
-        hipError_t ee = hipStreamEndCapture(s->cap_stream, &g);
-        if (st != LPIC_OK) { if (g) (void)hipGraphDestroy(g); return st; }
-        if (ee != hipSuccess) return fail(LPIC_EHIP, "graph capture: %s", hipGetErrorString(ee));
-        hipError_t ie = hipGraphInstantiate(&s->gexec[gi], g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (ie != hipSuccess) return fail(LPIC_EHIP, "graph instantiate: %s", hipGetErrorString(ie));
-      }
-      HIPCHK(hipGraphLaunch(s->gexec[gi], s->stream));
-      if (do_sort && s->nsegs > 0) swap_host_buffers(s);
-    } else {
-      CHK(enqueue_step(s, s->stream, do_sort, spread, diag, true, false, first_full, skip_last,
-                       rho, set, move));
-    }
-    if (move) set ^= 1;
-    if (skip_last && s->set2) set ^= 1;
-    move = false;
-    if (do_sort && s->nsegs > 0) {
-      ++s->sorts;
-      s->need_sort = false;
-      s->need_spread = false;
-      std::fill(s->inject_used.begin(), s->inject_used.end(), 0);
-      s->offsets_valid = true;
-    }
-    if (diag) s->diag_step = s->step + 1;
-    ++s->step;
-    CHK(run_hooks(s, LPIC_STAGE_LOOP_END));
+  const lpic_status st = run_steps(s, nsteps, set);
+  if (set) {   // an error in the middle of the call
+    const std::string keep = g_err;
+    s->lost = fields_back(s) != LPIC_OK;
+    (void)hipGetLastError();   // (reported here, not once more by the next launch)
+    g_err = keep;
   }
-  CHK(run_hooks(s, LPIC_STAGE_FINISH));
-  return LPIC_OK;
+  return st;
 }
 
 lpic_status lpic_get_species(lpic_sim* s, int32_t i, lpic_species* out) {

@@ -178,6 +178,62 @@ def second_set_current(H):
         H.L.lpic_sim_destroy(h)
 
 
+def failed_call(H):
+    """An error in the middle of a call whose fields are in the second set brings them back to
+    the caller's arrays, with their half of psi and their clock word."""
+    n = NX * NY * 8
+    cells = 8
+    psi = 2 * 4 * NY * 2 * cells * 8                      # two halves, a coefficient table after
+    table = 2 * 2 * cells * 3 * 8
+    for graph, steps, fail in ((True, 3, "instantiate"), (False, 3, "launch"), (False, 2, "launch")):
+        h = H.create(species=graph, graph=graph, open_x=True)
+        H.L.lpic_set_laser(h, 0, H.L.Laser(1, 12, 1.0, 1.0, 1.0, 3.0, 0.0, 0.0, 10.0))
+        H.L.lpic_set_pml(h, 0, H.L.Pml(cells, 3, 1, 0, -1.0, 1.0, 0.0))
+        H.L.lpic_step(h, 1)                               # (the first sort is not captured)
+        H.events()
+        p = H.stub.stub_newest(9 * n)
+        q = H.stub.stub_newest(psi + table)
+        arrays = [getattr(H.fields, k) for k, _ in H.L.Fields._fields_[:9]]
+        for k in range(9):
+            ctypes.memset(arrays[k], 0, n)
+            ctypes.memset(p + k * n, k + 1, n)
+        ctypes.memset(q, 0, psi // 2)
+        ctypes.memset(q + psi // 2, 5, psi // 2)
+        if fail == "instantiate":
+            H.stub.stub_fail_instantiate(1)               # the second step's variant
+        else:                                             # the third launch: the fields have moved
+            H.stub.stub_fail_launch(3 if steps == 3 else 2)
+        try:
+            H.L.lpic_step(h, steps)
+            raise AssertionError("no error")
+        except H.L.LpicError as e:
+            assert e.status == -2 and "stub error" in str(e), e
+        assert H.events().count("copy") == 11
+        for k in range(9):
+            assert ctypes.string_at(arrays[k], n) == bytes([k + 1]) * n, (graph, steps, k)
+        assert ctypes.string_at(q, psi // 2) == b"\5" * (psi // 2)
+        H.L.lpic_step(h, 3)                               # and the simulation goes on
+        # nothing to bring back before the first move is complete
+        if not graph:
+            H.stub.stub_fail_launch(1)
+            try:
+                H.L.lpic_step(h, 2)
+                raise AssertionError("no error")
+            except H.L.LpicError:
+                pass
+            assert "copy" not in H.events()
+            # fields that cannot be brought back: later calls are refused
+            H.stub.stub_fail_launch(2)
+            H.stub.stub_fail_copy(4)
+            for text in ("stub error", "lost"):
+                try:
+                    H.L.lpic_step(h, 2)
+                    raise AssertionError("no error")
+                except H.L.LpicError as e:
+                    assert e.status == -2 and text in str(e), e
+        H.L.lpic_sim_destroy(h)
+
+
 # ---- the tests -------------------------------------------------------------------------------
 def test_required_memory_before_the_second_field_set(tmp_path):
     _child("memory", tmp_path)
@@ -197,6 +253,10 @@ def test_clears_are_done_when_a_call_returns(tmp_path):
 
 def test_current_of_the_second_field_set(tmp_path):
     _child("second_set_current", tmp_path)
+
+
+def test_error_in_the_middle_of_a_call(tmp_path):
+    _child("failed_call", tmp_path)
 
 
 if __name__ == "__main__":
