@@ -857,15 +857,17 @@ __global__ __launch_bounds__((fused_block<R, DIM, G>())) __attribute__((amdgpu_w
 // its neighbourhood (escape_append), so a workgroup adds the windows of 256 of them in a box
 // in LDS (pick_box) and flushes it once: with an atomic per window entry the atomics were
 // what a launch took, whatever the number of workgroups (hot slab of 1.5M FP64 particles,
-// 20 steps late in the run: 5.0 ms with 128 workgroups and 5.2 with 1024, 3.8 with boxes).  Each workgroup takes a
-// contiguous share of the list.  skip_at: a list of at least this many entries was taken by
-// the re-binned path; only the clearing is left to do.
-template <typename R, int DIM>
+// 20 steps late in the run: 5.0 ms with 128 workgroups and 5.2 with 1024, 3.8 with boxes).
+// Each workgroup takes a contiguous share of the list.  BOX false: every entry straight into
+// memory, for the two lists of a re-binned step, which are short or empty (the boxes' code and
+// LDS are then all that a launch takes).  skip_at: a list of at least this many entries was
+// taken by the re-binned path; only the clearing is left to do.
+template <typename R, int DIM, bool BOX>
 __global__ __launch_bounds__(256) void k_escape(Tables T, int with_rho, double* kinetic,
                                                 int ke_to_diag, EscapeList esc, int skip_at,
                                                 int cap) {
   extern __shared__ double jm[];
-  __shared__ int red[4][13];
+  __shared__ int red[BOX ? 4 : 1][13];
   __shared__ int wrun[4];
   int64_t cnt = min((int64_t)esc.count[0], esc.capacity);
   if ((int)min(esc.count[0], 0x7fffffffu) >= skip_at) cnt = 0;
@@ -873,15 +875,16 @@ __global__ __launch_bounds__(256) void k_escape(Tables T, int with_rho, double* 
   const int planes = 3 + charge_planes(with_rho);
   // a short list is dealt out to all workgroups one entry at a time and deposits straight
   // into memory: a box's clearing, bounds and flush would be most of its time
-  const bool few = cnt <= (int64_t)gridDim.x * ESCAPE_FEW;
+  const bool few = !BOX || cnt <= (int64_t)gridDim.x * ESCAPE_FEW;
   const int64_t passes = (cnt + 255) / 256, per = (passes + gridDim.x - 1) / gridDim.x;
-  const int64_t it0 = few ? 0 : blockIdx.x * per, it1 = few ? 1 : min(it0 + per, passes);
+  const int64_t it0 = few ? 0 : blockIdx.x * per, it1 = few ? per : min(it0 + per, passes);
   NodeBox box;
 #pragma unroll
   for (int d = 0; d < 3; ++d) { box.at[d] = 0; box.lo[d] = 0; box.ext[d] = 1; }
   int brun = -1;                  // the box's run
   for (int64_t it = it0; it < it1; ++it) {
-    const int64_t i = few ? blockIdx.x + (int64_t)gridDim.x * threadIdx.x : it * 256 + 4 * lane + wave;
+    const int64_t i = few ? blockIdx.x + (int64_t)gridDim.x * (it * 256 + threadIdx.x)
+                          : it * 256 + 4 * lane + wave;
     int seg = 0, run = 0;
     bool live = false;
     EscPath<R> d;
@@ -907,49 +910,51 @@ __global__ __launch_bounds__(256) void k_escape(Tables T, int with_rho, double* 
       }
     }
     int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0}, v[3] = {0, 0, 0};
-    bool in = live && run == brun;
-    if (live) {
-      const RunDesc& r = run_of(T, run);
-      const int n[3] = {r.nx, r.ny, r.nz};
-      const bool cic = seg_of(T, seg).order == 1;
-#pragma unroll
-      for (int x = 0; x < DIM; ++x) {
-        if (cic) path_nodes<1>(d.o[x], d.e[x], lo[x], hi[x]);
-        else path_nodes<2>(d.o[x], d.e[x], lo[x], hi[x]);
-        v[x] = wrap_near(d.c[x] - box.at[x], n[x]) - box.lo[x];
-        in = in && v[x] + lo[x] >= 0 && v[x] + hi[x] < box.ext[x];
-      }
-    }
-    const int stray = few ? 0 : __syncthreads_count(live && !in);
-    if (stray > (brun >= 0 ? DEPOSIT_STRAY : 0)) {
-      if (brun >= 0) flush_box<R, DIM>(run_of(T, brun), box, planes, jm, with_rho == 3);
-      else
-        for (int q = threadIdx.x; q < cap * planes; q += 256) jm[q] = 0.0;
-      const uint64_t m = __ballot(live);
-      const int lead = m ? __ffsll((unsigned long long)m) - 1 : 0;
-      const int lr = __shfl(run, lead, 64);
-      if (lane == 0) wrun[wave] = m ? lr : -1;
-      __syncthreads();
-      brun = uniform(wrun[0] >= 0 ? wrun[0] : (wrun[1] >= 0 ? wrun[1] : (wrun[2] >= 0 ? wrun[2] : wrun[3])));
-      const RunDesc& r = run_of(T, brun);
-      const int n[3] = {r.nx, r.ny, r.nz};
-      const bool here = live && run == brun;
-      box = pick_box<DIM>(here, d.c, lo, hi, n, cap, red);
-      in = here;
-      if (here) {
+    bool in = BOX && live && run == brun;
+    if constexpr (BOX) {
+      if (live) {
+        const RunDesc& r = run_of(T, run);
+        const int n[3] = {r.nx, r.ny, r.nz};
+        const bool cic = seg_of(T, seg).order == 1;
 #pragma unroll
         for (int x = 0; x < DIM; ++x) {
+          if (cic) path_nodes<1>(d.o[x], d.e[x], lo[x], hi[x]);
+          else path_nodes<2>(d.o[x], d.e[x], lo[x], hi[x]);
           v[x] = wrap_near(d.c[x] - box.at[x], n[x]) - box.lo[x];
           in = in && v[x] + lo[x] >= 0 && v[x] + hi[x] < box.ext[x];
         }
       }
-      __syncthreads();
+      const int stray = few ? 0 : __syncthreads_count(live && !in);
+      if (stray > (brun >= 0 ? DEPOSIT_STRAY : 0)) {
+        if (brun >= 0) flush_box<R, DIM>(run_of(T, brun), box, planes, jm, with_rho == 3);
+        else
+          for (int q = threadIdx.x; q < cap * planes; q += 256) jm[q] = 0.0;
+        const uint64_t m = __ballot(live);
+        const int lead = m ? __ffsll((unsigned long long)m) - 1 : 0;
+        const int lr = __shfl(run, lead, 64);
+        if (lane == 0) wrun[wave] = m ? lr : -1;
+        __syncthreads();
+        brun = uniform(wrun[0] >= 0 ? wrun[0] : (wrun[1] >= 0 ? wrun[1] : (wrun[2] >= 0 ? wrun[2] : wrun[3])));
+        const RunDesc& r = run_of(T, brun);
+        const int n[3] = {r.nx, r.ny, r.nz};
+        const bool here = live && run == brun;
+        box = pick_box<DIM>(here, d.c, lo, hi, n, cap, red);
+        in = here;
+        if (here) {
+#pragma unroll
+          for (int x = 0; x < DIM; ++x) {
+            v[x] = wrap_near(d.c[x] - box.at[x], n[x]) - box.lo[x];
+            in = in && v[x] + lo[x] >= 0 && v[x] + hi[x] < box.ext[x];
+          }
+        }
+        __syncthreads();
+      }
     }
     if (live) {
       const SegDesc& s = seg_of(T, seg);
       const RunDesc& r = run_of(T, run);
       const PushConst<R> k = push_const<R>(r, s);
-      if (in) {
+      if (BOX && in) {
         const BoxAcc<R> B{jm, box.ext[0], box.ext[0] * box.ext[1],
                           box.ext[0] * box.ext[1] * box.ext[2]};
         if (s.order == 1) deposit<DIM, 1>(B, v, d.o, d.e, d.w, d.vz, k, d.rho);
@@ -962,7 +967,7 @@ __global__ __launch_bounds__(256) void k_escape(Tables T, int with_rho, double* 
     }
   }
   __syncthreads();
-  if (brun >= 0) flush_box<R, DIM>(run_of(T, brun), box, planes, jm, with_rho == 3);
+  if (BOX && brun >= 0) flush_box<R, DIM>(run_of(T, brun), box, planes, jm, with_rho == 3);
   // the last workgroup to finish clears the list (every workgroup has read the count by
   // then; no fence: nothing this launch wrote is read before the launch ends)
   __syncthreads();
@@ -1041,12 +1046,12 @@ static int escape_blocks(int dim, int64_t slots) {
   return (int)std::min<int64_t>(ESCAPE_BLOCKS, (slots + 255) / 256);
 }
 
-template <typename R, int D>
+template <typename R, int D, bool BOX>
 static void launch_escape(const Tables& T, int with_rho, double* kinetic, int ke_to_diag,
-                          const EscapeList& esc, int skip_at, int blocks, int smem,
-                          hipStream_t st) {
-  k_escape<R, D><<<blocks, 256, smem, st>>>(T, with_rho, kinetic, ke_to_diag, esc, skip_at,
-                                            smem / 8 / (3 + charge_planes(with_rho)));
+                          const EscapeList& esc, int skip_at, int blocks, hipStream_t st) {
+  const int smem = BOX ? escape_smem(D) : 0;
+  k_escape<R, D, BOX><<<blocks, 256, smem, st>>>(T, with_rho, kinetic, ke_to_diag, esc, skip_at,
+                                                 smem / 8 / (3 + charge_planes(with_rho)));
 }
 
 void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size_t smem,
@@ -1068,18 +1073,18 @@ void launch_fused(const Tables& T, int prec, int dim, int geo, int nblocks, size
                                              rb->esc2, false, 0, jshift,
                                              PassList{rb->items, esc.rec ? rb->rec : nullptr},
                                              st)));
-    // (a list below the threshold is a short one for as many workgroups, and needs no LDS; the
-    // second pass's list is normally empty: 128 workgroups with their boxes of LDS cost a step
-    // of 2D or 3D some 4 us)
+    // (a list below the threshold is a short one for as many workgroups, and the second pass's
+    // list is normally empty: without boxes for either.  128 workgroups with their boxes of LDS
+    // cost a step of 2D or 3D some 4 us)
     const int few = (rb->threshold + ESCAPE_FEW - 1) / ESCAPE_FEW;
-    LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, rb->threshold,
-                                            few, 0, st)));
-    LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, rb->esc2, 0x7fffffff,
-                                            few, escape_smem(2), st)));
+    LPIC_PD(prec, dim, (launch_escape<R, D, false>(T, with_rho, kinetic, ke_to_diag, esc,
+                                                   rb->threshold, few, st)));
+    LPIC_PD(prec, dim, (launch_escape<R, D, false>(T, with_rho, kinetic, ke_to_diag, rb->esc2,
+                                                   0x7fffffff, few, st)));
   } else {
     const int blocks = escape_blocks(dim, esc.capacity);
-    LPIC_PD(prec, dim, (launch_escape<R, D>(T, with_rho, kinetic, ke_to_diag, esc, 0x7fffffff,
-                                            blocks, escape_smem(dim), st)));
+    LPIC_PD(prec, dim, (launch_escape<R, D, true>(T, with_rho, kinetic, ke_to_diag, esc,
+                                                  0x7fffffff, blocks, st)));
   }
 }
 
@@ -1093,7 +1098,7 @@ static hipError_t set_smem(size_t smem, size_t smem_occ, int* blocks_per_cu) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if constexpr (D == 3)
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_escape<R, D>,
+      e = hipFuncSetAttribute((const void*)k_escape<R, D, true>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, escape_smem(D));
   if (e != hipSuccess) return e;
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_fused<R, D, G, false>,

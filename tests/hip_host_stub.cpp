@@ -145,9 +145,9 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shared, void** st
   *stream = config.stream;
   return 0;
 }
-int hipLaunchKernel(const void* f, Dim3 grid, Dim3, void**, size_t, void*) {
+int hipLaunchKernel(const void* f, Dim3 grid, Dim3, void**, size_t shared, void*) {
   if (due(fail_launch)) return fail(1);
-  log("launch " + names[f] + " " + std::to_string(grid.x));
+  log("launch " + names[f] + " " + std::to_string(grid.x) + " " + std::to_string(shared));
   return 0;
 }
 }

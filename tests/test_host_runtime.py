@@ -234,6 +234,15 @@ def failed_call(H):
         H.L.lpic_sim_destroy(h)
 
 
+def rebinned(H):
+    """The two escape lists of a re-binned step are short or empty: no deposit boxes in LDS."""
+    h = H.create(flags=H.L.ESCAPE_REBIN)
+    H.L.lpic_step(h, 2)
+    e = [x.split() for x in H.events() if "k_escape" in x]
+    assert len(e) == 4
+    assert all(x[3] == "0" for x in e), e
+
+
 # ---- the tests -------------------------------------------------------------------------------
 def test_required_memory_before_the_second_field_set(tmp_path):
     _child("memory", tmp_path)
@@ -257,6 +266,10 @@ def test_current_of_the_second_field_set(tmp_path):
 
 def test_error_in_the_middle_of_a_call(tmp_path):
     _child("failed_call", tmp_path)
+
+
+def test_escape_launches_of_a_rebinned_step(tmp_path):
+    _child("rebinned", tmp_path)
 
 
 if __name__ == "__main__":
