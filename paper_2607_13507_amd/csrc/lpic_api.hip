@@ -1058,8 +1058,11 @@ lpic_status field_sets(lpic_sim* s) {
     HIPCHK(hipMemcpy(s->runs2_d, runs2.data(), sizeof(RunDesc) * s->nruns, hipMemcpyHostToDevice));
     // without species nothing clears the second set's J: it starts and stays zero (the rest of
     // the set is written before it is read)
-    for (int r = 0; s->nsegs == 0 && r < s->nruns; ++r)
-      HIPCHK(hipMemset(runs2[r].f[F_JX], 0, 3 * align256(ncells(&s->grids[r]) * size)));
+    for (int r = 0; s->nsegs == 0 && r < s->nruns; ++r) {
+      launch_zero_u32((uint32_t*)runs2[r].f[F_JX],
+                      (int64_t)(3 * align256(ncells(&s->grids[r]) * size) / 4), s->stream);
+      CHK(last_launch("second J clear"));
+    }
   }
   s->mid_tx = tx;
   s->mid_ty = ty;
@@ -1220,7 +1223,10 @@ lpic_status configure(lpic_sim* s) {
     s->esc_capacity = std::max<int64_t>(pbase, 1);
     ALLOC(s->esc_items, sizeof(unsigned long long) * s->esc_capacity);
     ALLOC(s->esc_count, 256);
-    HIPCHK(hipMemset(s->esc_count, 0, 256));
+    // (this clear and those below in stream order: the caller's stream need not wait for the
+    // null stream, on which a memset runs; a wait for it costs a set-up 0.1 ms)
+    launch_zero_u32(s->esc_count, 64, s->stream);
+    CHK(last_launch("escape counters clear"));
   }
   if (t.flags & LPIC_ESCAPE_REBIN) {
     if (!s->rb_items) {
@@ -1234,7 +1240,7 @@ lpic_status configure(lpic_sim* s) {
         if (s->prec == LPIC_F32_CELLOFS) ALLOC(s->esc_keys, sizeof(int32_t) * s->esc_capacity);
       }
       ALLOC(s->esc2_count, 256);
-      HIPCHK(hipMemset(s->esc2_count, 0, 256));
+      launch_zero_u32(s->esc2_count, 64, s->stream);
     }
     Rebin& rb = s->rb;
     ALLOC(rb.counts, sizeof(int32_t) * (s->nbins + 1));
@@ -1242,8 +1248,9 @@ lpic_status configure(lpic_sim* s) {
     ALLOC(rb.cursor, sizeof(int32_t) * (s->nbins + 1));
     ALLOC(rb.chunks, sizeof(Chunk) * std::max<int64_t>(1, maxch));
     ALLOC(rb.nchunks, 256);
-    HIPCHK(hipMemset(rb.counts, 0, sizeof(int32_t) * (s->nbins + 1)));
-    HIPCHK(hipMemset(rb.nchunks, 0, 256));
+    launch_zero_u32((uint32_t*)rb.counts, s->nbins + 1, s->stream);
+    launch_zero_u32((uint32_t*)rb.nchunks, 64, s->stream);
+    CHK(last_launch("re-binning clear"));
     rb.threshold = REBIN_THRESHOLD;
     rb.nbins = s->nbins;
     rb.nvirt = s->nvirt;
@@ -1278,10 +1285,7 @@ lpic_status configure(lpic_sim* s) {
 #undef ALLOC
   s->need_sort = true;
   s->offsets_valid = false;
-  CHK(field_sets(s));
-  // the buffers were cleared on the null stream, which the caller's stream need not wait for
-  HIPCHK(hipStreamSynchronize(nullptr));
-  return LPIC_OK;
+  return field_sets(s);
 }
 
 void swap_host_buffers(lpic_sim* s) {

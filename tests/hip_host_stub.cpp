@@ -1,7 +1,7 @@
 // A HIP runtime without a GPU, for host-side tests of liblpic.so: device memory is host memory
-// from a budget, kernels do nothing, and what a stream would be given is written to a log
-// (launches inside a captured graph when the graph is launched).  Loaded before the library
-// under the HIP runtime's soname, it stands in for it.
+// from a budget, kernels do nothing (but for the one that fills with zeros), and what a stream
+// would be given is written to a log (launches inside a captured graph when the graph is
+// launched).  Loaded before the library under the HIP runtime's soname, it stands in for it.
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -145,8 +145,10 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shared, void** st
   *stream = config.stream;
   return 0;
 }
-int hipLaunchKernel(const void* f, Dim3 grid, Dim3, void**, size_t shared, void*) {
+int hipLaunchKernel(const void* f, Dim3 grid, Dim3, void** args, size_t shared, void*) {
   if (due(fail_launch)) return fail(1);
+  if (!capturing && names[f].find("k_fill_zero_u32") != std::string::npos)
+    memset(*(void**)args[0], 0, 4 * *(int64_t*)args[1]);
   log("launch " + names[f] + " " + std::to_string(grid.x) + " " + std::to_string(shared));
   return 0;
 }
