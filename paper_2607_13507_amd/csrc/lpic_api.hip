@@ -874,7 +874,6 @@ struct lpic_sim {
   // fused 2D field update between steps (launch_yee_mid): its tile, 0 where the updates run as
   // separate kernels; it runs between steps without diagnostics while set2 is there
   int mid_tx = 0, mid_ty = 0, mid_ntiles = 0;
-  bool mid_divides = false;                  // the tile divides every box
   bool rows = false;                         // every box satisfies yee_rows
   int32_t* mid_pfx_d = nullptr;              // nruns + 1 prefix of field tiles
   void* set2 = nullptr;                      // E, B and J of the second field set
@@ -978,7 +977,6 @@ lpic_status run_hooks(lpic_sim* s, int stage) {
   return LPIC_OK;
 }
 
-// (Re)build everything that depends on the options: tiling, bins, chunk tables.
 // Bytes of the two halves of a run's PML auxiliary values (the coefficient table follows).
 size_t pml_psi_bytes(const lpic_grid* g, int cells, int prec) {
   return (size_t)2 * 4 * g->ny * (g->ndim == 3 ? g->nz : 1) * 2 * cells *
@@ -1004,8 +1002,8 @@ lpic_status field_sets(lpic_sim* s) {
       while (tx >= 8 && s->grids[r].nx % tx) tx >>= 1;
       while (ty >= 4 && s->grids[r].ny % ty) ty >>= 1;
     }
-    s->mid_divides = tx >= 8 && ty >= 4;
-    if (!s->mid_divides || s->windows || tx * ty < 256) {
+    const bool divides = tx >= 8 && ty >= 4;
+    if (!divides || tx * ty < 256) {
       // (a tile below 256 cells leaves threads idle and reads half its cells again as halo;
       // 1000 x 600 cells in FP64: 42 us with 8 x 8 tiles that divide it, 26 with 64 x 16)
       int nxm = INT_MAX, nym = INT_MAX;
@@ -1013,7 +1011,7 @@ lpic_status field_sets(lpic_sim* s) {
         nxm = std::min(nxm, (int)s->grids[r].nx);
         nym = std::min(nym, (int)s->grids[r].ny);
       }
-      if (!s->mid_divides || (nxm >= 64 && nym >= 16)) {
+      if (!divides || (nxm >= 64 && nym >= 16)) {
         tx = MID_MAX_TX;
         ty = MID_MAX_TY;
         while (tx > 8 && 2 * nxm <= tx) tx >>= 1;
@@ -1070,6 +1068,7 @@ lpic_status field_sets(lpic_sim* s) {
   return LPIC_OK;
 }
 
+// (Re)build everything that depends on the options: tiling, bins, chunk tables.
 lpic_status configure(lpic_sim* s) {
   drop_graphs(s);
   lpic_tiling t = s->opt.tiling;

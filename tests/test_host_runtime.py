@@ -243,6 +243,23 @@ def rebinned(H):
     assert all(x[3] == "0" for x in e), e
 
 
+def moved_window(H):
+    """A simulation whose window has moved keeps the fused field update, with the same tile
+    before and after its options are set again."""
+    H.grid.nx, H.grid.ny = 96, 24
+    h = H.create(open_x=True)
+
+    def updates():
+        H.L.lpic_step(h, 3)
+        return [e for e in H.events() if "k_yee_mid" in e]
+    first = updates()
+    assert len(first) == 2 and H.tile(h) == (32, 8)
+    H.L.lpic_window_shift(h, 0, 5)
+    assert updates() == first
+    H.L.lpic_set_options(h, H.L.Options(H.L.Tiling(16, 16, 1, 5, 256, 0), 10, 0, 1, 0))
+    assert updates() == first
+
+
 # ---- the tests -------------------------------------------------------------------------------
 def test_required_memory_before_the_second_field_set(tmp_path):
     _child("memory", tmp_path)
@@ -270,6 +287,10 @@ def test_error_in_the_middle_of_a_call(tmp_path):
 
 def test_escape_launches_of_a_rebinned_step(tmp_path):
     _child("rebinned", tmp_path)
+
+
+def test_fused_update_of_a_moved_window(tmp_path):
+    _child("moved_window", tmp_path)
 
 
 if __name__ == "__main__":
