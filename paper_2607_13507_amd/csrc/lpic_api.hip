@@ -1222,8 +1222,8 @@ lpic_status configure(lpic_sim* s) {
     s->esc_capacity = std::max<int64_t>(pbase, 1);
     ALLOC(s->esc_items, sizeof(unsigned long long) * s->esc_capacity);
     ALLOC(s->esc_count, 256);
-    // (this clear and those below in stream order: the caller's stream need not wait for the
-    // null stream, on which a memset runs; a wait for it costs a set-up 0.1 ms)
+    // (this clear and those below in stream order: a memset runs on the null stream, which the
+    // caller's stream need not wait for)
     launch_zero_u32(s->esc_count, 64, s->stream);
     CHK(last_launch("escape counters clear"));
   }

@@ -26,7 +26,7 @@ namespace lpic {
 // escape path for 8 x 4 x 4 tilings with halo 4 (its particles lie inside their present
 // tile, so a halo of 3 always holds their stencils).  Geometry 8 is the same region without
 // the layer pad, for the FP32 steps that carry one charge plane (chained charge, see
-// k_fused): it still fits two 512-thread workgroups per CU (80.7 KB each).  Geometry 9 is
+// k_fused): it still fits two 512-thread workgroups per CU (81.5 KB each, of 163.8).  Geometry 9 is
 // the padded region with 1024-thread workgroups, for FP32 steps with both charge planes:
 // they leave room for one workgroup per CU, which then brings all sixteen waves by itself.
 struct GeoFix { int tx, ty, tz, halo, pz; };
@@ -244,8 +244,12 @@ __device__ __forceinline__ bool escape_push(const RunDesc& r, const SegDesc& s, 
 //   Otherwise the shared list; in 2D through one in LDS (list, cap entries), so that the
 //     particles of a tile reach it side by side and share a deposit box in k_escape.  Where a
 //     tile loses most of its particles (a wake's bubble) the workgroup that meets them is no
-//     place to push them: the last one ends long after the others (14.3 ms for 20 steps of
-//     the 8192 x 512 wakefield box against 13.6).
+//     place to push them: the last one ends long after the others.
+//   The line between the two (FUSED_KEEP) goes by the slots of the simulation, which bound that
+//   tail, not by the escapes per tile, which cause it.  With the list and with every workgroup
+//   pushing its own, above the line: 8192 x 512 wakefield box, 15.2M FP32 particles, 12.92 and
+//   13.74 ms per 20 steps; laser slab of 16.8M FP32 particles 9.83 and 9.91, 64 slabs of 180M
+//   70.1 and 71.4; but a hot slab of 1.5M FP64 particles late in the run 4.00 and 3.71.
 struct EscapeOut {
   EscapeList list;
   int32_t* count;              // LDS: entries kept, or in the LDS list
@@ -254,9 +258,6 @@ struct EscapeOut {
   int64_t base;                // KEEP
 };
 
-// Append the lanes that want it to the escape list (one reservation per wave), with their
-// escape records when the list keeps them (3D only: the 2D body has no registers to spare
-// for the record's words, and 2D particles rarely leave their regions).
 // Entry k of the escape list: the particle's record and the bin of the tile it is in.
 template <typename R, int DIM>
 __device__ __forceinline__ void escape_record(const EscapeList& esc, int64_t k,
@@ -271,6 +272,9 @@ __device__ __forceinline__ void escape_record(const EscapeList& esc, int64_t k,
                     : s.bin_base + r.ntiles;
 }
 
+// Append the lanes that want it to the workgroup's list or the shared one (one reservation per
+// wave), there with their escape records when the list keeps them (3D only: the 2D body has no
+// registers to spare for the record's words, and 2D particles rarely leave their regions).
 template <typename R, int DIM, bool KEEP>
 __device__ __forceinline__ void escape_append(const EscapeOut& out, bool want, int seg,
                                               int32_t p, const PartPtrs<R>& q,

@@ -127,7 +127,8 @@ struct EscapeList {
 // out evenly instead of in runs that share a deposit box.
 constexpr int ESCAPE_BLOCKS = 128, ESCAPE_FEW = 64;
 // Slots up to which a 2D simulation without the re-binned path pushes escaped particles in
-// the workgroup that meets them: above, a launch over the list is 1% of a step or less.
+// the workgroup that meets them: a small box saves the launch over the list, 6 us of each of
+// its steps; a large one may wait for the workgroup with the most (EscapeOut: both sides).
 constexpr int64_t FUSED_KEEP = 1 << 20;
 constexpr size_t FUSED_LIST = 512;    // entries of a 2D workgroup's list in LDS
 

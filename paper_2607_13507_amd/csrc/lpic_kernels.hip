@@ -2249,9 +2249,8 @@ void launch_gather_push(const Tables& T, int prec, int dim, int nblocks, void* o
 
 void launch_deposit(const Tables& T, int prec, int dim, int nblocks, const void* old,
                     int with_rho, hipStream_t st) {
-  // LDS per workgroup: three workgroups a CU.  Passes per
-  // workgroup: as many as leave about eight workgroups a CU, so that a small call still
-  // covers the chip.
+  // LDS per workgroup: three workgroups a CU.  Passes per workgroup: as many as leave about
+  // eight workgroups a CU, so that a small call still covers the chip.
   const size_t smem = 52 * 1024;
   const int cap = (int)(smem / 8 / (with_rho ? 5 : 3));
   const int per = nblocks >= 16384 ? 8 : (nblocks >= 2048 ? nblocks / 2048 : 1);
