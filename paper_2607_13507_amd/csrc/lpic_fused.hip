@@ -421,8 +421,9 @@ __device__ __forceinline__ bool push_on_chip(const RunDesc& r, const Region& g, 
 // again before every wave has passed the next barrier.  The cells of the next round are loaded
 // while this one is pushed.  Escaped particles wait in LDS and go to the escape list by the
 // hundred: a reservation per round kept every round waiting for a global atomic and for the
-// loads of a few records.  What bounds it now is the body itself: LDS 67% and the vector units
-// 65% of the busy cycles, half of the LDS cycles bank conflicts of random positions.
+// loads of a few records.  What bounds it now is the body itself: over a sort interval LDS 61%
+// and the vector units 60% of the busy cycles, over half of the LDS cycles bank conflicts of
+// random positions.
 // 20 steps of 256^3 FP32, 134M particles: three barriers and a reservation per round 369 ms,
 // one barrier 355, with the ring instead of a push per round 347 (100 x 84 x 60 FP64, 10
 // steps: 9.76, 9.74, 9.54 ms).  768 instead of 512 threads in FP64 (three waves per SIMD, 168
